@@ -2,7 +2,7 @@
 // their forward, input-gradient and weight-gradient forms.
 //
 //   C[m, n] = sum_k A(m, k) * B(n, k),  fp32 accumulation on
-//   v_mfma_f32_32x32x16_bf16.
+//   v_mfma_f32_16x16x32_bf16 (32x32x16 in the register-staged kernel).
 //
 // Operands whose contraction index is contiguous in memory (activations in
 // the forward, weights [out, in] in the forward) are copied to LDS with
@@ -26,6 +26,7 @@
 // so each XCD is given its own block of the tile grid, walked M-fastest in
 // groups of row tiles, which keeps the operand panels it shares in its L2.
 #include <algorithm>
+#include <type_traits>
 
 #include "common.hpp"
 #include "kernels.hpp"
@@ -215,36 +216,32 @@ __device__ __forceinline__ void store_tile(const GemmArgs &p, const f32x16_t (&a
 constexpr int kEpiRows = 64;
 
 template <Epi EPI, int BM, int BN, int WM, int WN>
-__device__ __forceinline__ void store_tile_lds(const GemmArgs &p, const f32x16_t (&acc)[BM / WM / 32][BN / WN / 32],
+__device__ __forceinline__ void store_tile_lds(const GemmArgs &p, const f32x4_t (&acc)[BM / WM / 16][BN / WN / 16],
                                                int m0, int n0, int wm, int wn, int lane, float *lds) {
   constexpr int NT = WM * WN * 64;
-  constexpr int WTM = BM / WM, WTN = BN / WN, FM = WTM / 32, FN = WTN / 32;
+  constexpr int WTM = BM / WM, WTN = BN / WN, FM = WTM / 16, FN = WTN / 16;
   constexpr int LDR = BN + 4;  // floats per LDS row (16-byte pad)
   constexpr int NCH = BM / kEpiRows;
-  static_assert(BM % kEpiRows == 0 && kEpiRows % 32 == 0, "epilogue chunking");
+  static_assert(BM % kEpiRows == 0 && kEpiRows % 16 == 0, "epilogue chunking");
   constexpr bool kHasBias = EPI == Epi::kBias || EPI == Epi::kBiasResid || EPI == Epi::kBiasGelu;
   // a second per-element input: the residual, or the saved pre-activation u
   constexpr bool kHasR = EPI == Epi::kBiasResid || EPI == Epi::kResid || EPI == Epi::kGeluGrad;
   constexpr int PRB = BN / 8;                        // 16-byte bf16 segments per row
   constexpr int SEGS = (kEpiRows * PRB + NT - 1) / NT;  // per thread and chunk
   const int tid = threadIdx.x;
-  const int lrow = lane & 31;
+  // a lane owns row lane % 16 and four columns of each 16x16 fragment
+  const int lrow = lane & 15, lcol = (lane >> 4) * 4;
 
   // Every load of the epilogue is issued before its first store: loads and
   // stores retire in issue order, so a load issued behind the stores of the
   // previous chunk would wait for them.
-  // (the 256-wide tile with both a bias and a residual has no registers to
-  // spare for the bias: it loads the bias per chunk instead)
-  constexpr bool kPreBias = kHasBias && !(kHasR && BN > 192);
-  u32x2_t bias_w[kPreBias ? FN : 1][4];
-  if constexpr (kPreBias) {
+  u32x2_t bias_w[kHasBias ? FN : 1];
+  if constexpr (kHasBias) {
 #pragma unroll
-    for (int j = 0; j < FN; ++j)
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int nb = n0 + wn * WTN + j * 32 + q * 8 + (lane >> 5) * 4;
-        bias_w[j][q] = nb < p.N ? *reinterpret_cast<const u32x2_t *>(p.bias + nb) : u32x2_t{0u, 0u};
-      }
+    for (int j = 0; j < FN; ++j) {
+      const int nb = n0 + wn * WTN + j * 16 + lcol;
+      bias_w[j] = nb < p.N ? *reinterpret_cast<const u32x2_t *>(p.bias + nb) : u32x2_t{0u, 0u};
+    }
   }
   u32x4_t rin[kHasR ? NCH : 1][kHasR ? SEGS : 1];
   if constexpr (kHasR) {
@@ -264,32 +261,19 @@ __device__ __forceinline__ void store_tile_lds(const GemmArgs &p, const f32x16_t
     __syncthreads();  // LDS free (k-loop reads or the previous chunk's readers done)
 #pragma unroll
     for (int i = 0; i < FM; ++i) {
-      const int r0 = wm * WTM + i * 32;  // fragment's first tile row
+      const int r0 = wm * WTM + i * 16;  // fragment's first tile row
       if (r0 < c * kEpiRows || r0 >= (c + 1) * kEpiRows) continue;
       const int rl = r0 - c * kEpiRows + lrow;
 #pragma unroll
       for (int j = 0; j < FN; ++j) {
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const int cl = wn * WTN + j * 32 + q * 8 + (lane >> 5) * 4;
-          f32x4_t v{acc[i][j][q * 4], acc[i][j][q * 4 + 1], acc[i][j][q * 4 + 2], acc[i][j][q * 4 + 3]};
-          if constexpr (kPreBias) {
-            v[0] += lo_bf(bias_w[j][q][0]);
-            v[1] += hi_bf(bias_w[j][q][0]);
-            v[2] += lo_bf(bias_w[j][q][1]);
-            v[3] += hi_bf(bias_w[j][q][1]);
-          } else if constexpr (kHasBias) {
-            const int nb = n0 + cl;
-            if (nb < p.N) {
-              const u32x2_t bw = *reinterpret_cast<const u32x2_t *>(p.bias + nb);
-              v[0] += lo_bf(bw[0]);
-              v[1] += hi_bf(bw[0]);
-              v[2] += lo_bf(bw[1]);
-              v[3] += hi_bf(bw[1]);
-            }
-          }
-          *reinterpret_cast<f32x4_t *>(lds + rl * LDR + cl) = v;
+        f32x4_t v = acc[i][j];
+        if constexpr (kHasBias) {
+          v[0] += lo_bf(bias_w[j][0]);
+          v[1] += hi_bf(bias_w[j][0]);
+          v[2] += lo_bf(bias_w[j][1]);
+          v[3] += hi_bf(bias_w[j][1]);
         }
+        *reinterpret_cast<f32x4_t *>(lds + rl * LDR + wn * WTN + j * 16 + lcol) = v;
       }
     }
     __syncthreads();
@@ -574,11 +558,16 @@ struct NtTile {
   __device__ static __forceinline__ int off(int r, int c) { return r * RB + ((c ^ ((r / RP) % CPR)) << 4); }
 };
 
+// Chunk swizzle of k-row k of a transposed tile: the eight k-rows that a
+// half-wave of transpose reads touches (0..3 and 8..11 of 16, or 4..7 and
+// 12..15) go to eight disjoint 32-byte ranges.
+__device__ __forceinline__ int t_swz(int k) { return ((k & 3) << 1) | (((k >> 3) & 1) << 3); }
+
 template <int ROWS>
 struct TTile {
   static constexpr int TROWS = ROWS <= 128 ? 128 : 256;  // padded k-row length
-  static_assert(ROWS <= 256 && ROWS % 32 == 0, "transposed tile width");
-  __device__ static __forceinline__ int off(int k, int j) { return k * (TROWS * 2) + ((j ^ ((k & 3) << 2)) << 4); }
+  static_assert(ROWS <= 256 && ROWS % 16 == 0, "transposed tile width");
+  __device__ static __forceinline__ int off(int k, int j) { return k * (TROWS * 2) + ((j ^ t_swz(k)) << 4); }
 };
 
 template <int ROWS, int BK, int NW, bool TRANS>
@@ -608,7 +597,7 @@ struct DirectLoader {
       } else {
         constexpr int TR = TTile<ROWS>::TROWS;
         const int k = o / (TR * 2), pch = (o % (TR * 2)) >> 4;
-        const int j = pch ^ ((k & 3) << 2);
+        const int j = pch ^ t_swz(k);
         voff[i] = static_cast<uint32_t>((k * static_cast<long>(ld) + r0 + j * 8) * 2);
         if (j * 8 < ROWS) live |= 1u << i;
       }
@@ -625,35 +614,38 @@ struct DirectLoader {
   }
 };
 
-// Per-lane LDS byte offsets of one operand's MFMA fragments (stage-relative).
+// Per-lane LDS byte offsets of one operand's 16x16x32 MFMA fragments
+// (stage-relative): the lane holds row lane % 16 of the fragment and
+// contraction elements 8 * (lane / 16) .. + 7 of a 32-wide step.
 template <int ROWS, int BK, int F, bool TRANS>
 struct FragAddr {
-  static constexpr int KS = BK / 16;
-  // non-transposed: one address per k-step (fragments add 32 rows);
-  // transposed: two per fragment (k-steps add 16 k-rows).
-  static constexpr int N = TRANS ? 2 * F : KS;
+  static constexpr int KS = BK / 32;
+  // non-transposed: one address per k-step (fragments add 16 rows);
+  // transposed: one per fragment (k-steps add 32 k-rows, the second half of
+  // the eight elements 4 k-rows).
+  static constexpr int N = TRANS ? F : KS;
   int off[N];
   __device__ __forceinline__ void init(int rbase, int lane) {
     if constexpr (!TRANS) {
 #pragma unroll
-      for (int kk = 0; kk < KS; ++kk) off[kk] = NtTile<BK>::off(rbase + (lane & 31), kk * 2 + (lane >> 5));
+      for (int kk = 0; kk < KS; ++kk) off[kk] = NtTile<BK>::off(rbase + (lane & 15), kk * 4 + (lane >> 4));
     } else {
-      const int k = 8 * (lane >> 5) + ((lane & 15) >> 2);
+      const int k = 8 * (lane >> 4) + ((lane & 15) >> 2);
 #pragma unroll
       for (int f = 0; f < F; ++f) {
-        const int n = rbase + f * 32 + 16 * ((lane >> 4) & 1) + 4 * (lane & 3);
-        off[2 * f] = TTile<ROWS>::off(k, n >> 3) + (n & 7) * 2;
-        off[2 * f + 1] = TTile<ROWS>::off(k + 4, n >> 3) + (n & 7) * 2;
+        const int n = rbase + f * 16 + 4 * (lane & 3);
+        off[f] = TTile<ROWS>::off(k, n >> 3) + (n & 7) * 2;
       }
     }
   }
   __device__ __forceinline__ bf16x8_t get(const lds_char *tile, int f, int kk) const {
     if constexpr (!TRANS) {
       return *reinterpret_cast<const __attribute__((address_space(3))) bf16x8_t *>(tile + off[kk] +
-                                                                                     f * 32 * BK * 2);
+                                                                                     f * 16 * BK * 2);
     } else {
       constexpr int TR = TTile<ROWS>::TROWS;
-      return lds_read_tr(tile + off[2 * f] + kk * 16 * TR * 2, tile + off[2 * f + 1] + kk * 16 * TR * 2);
+      const lds_char *q = tile + off[f] + kk * 32 * TR * 2;
+      return lds_read_tr(q, q + 4 * TR * 2);
     }
   }
 };
@@ -677,11 +669,11 @@ template <int BM, int BN, int BK, int WM, int WN, int STAGES, bool AT, bool BT, 
 __global__ __launch_bounds__(WM *WN * 64, 1) void gemm_lds_kernel(GemmArgs p, uint32_t a_bytes, uint32_t b_bytes) {
   constexpr int NW = WM * WN;
   constexpr int WTM = BM / WM, WTN = BN / WN;
-  constexpr int FM = WTM / 32, FN = WTN / 32;
-  constexpr int KS = BK / 16;
+  constexpr int FM = WTM / 16, FN = WTN / 16;
+  constexpr int KS = BK / 32;
   constexpr int A_BYTES = DirectLoader<BM, BK, NW, AT>::BYTES, B_BYTES = DirectLoader<BN, BK, NW, BT>::BYTES;
   constexpr int STAGE = A_BYTES + B_BYTES;
-  static_assert(STAGES >= 2 && BK % 16 == 0, "pipeline shape");
+  static_assert(STAGES >= 2 && BK % 32 == 0, "pipeline shape");
   extern __shared__ __attribute__((aligned(1024))) char smem_raw[];
   const lds_char *smem = (const lds_char *)(smem_raw);  // generic -> LDS address space
 
@@ -708,11 +700,11 @@ __global__ __launch_bounds__(WM *WN * 64, 1) void gemm_lds_kernel(GemmArgs p, ui
   fa.init(wm * WTM, lane);
   fb.init(wn * WTN, lane);
 
-  f32x16_t acc[FM][FN];
+  f32x4_t acc[FM][FN];
 #pragma unroll
   for (int i = 0; i < FM; ++i)
 #pragma unroll
-    for (int j = 0; j < FN; ++j) acc[i][j] = f32x16_t{};
+    for (int j = 0; j < FN; ++j) acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 
   // Weight gradient: the bias gradient db[m] = sum_k A(m, k) is summed from
   // the A fragments already in registers by the first wave column of the
@@ -757,44 +749,25 @@ __global__ __launch_bounds__(WM *WN * 64, 1) void gemm_lds_kernel(GemmArgs p, ui
     // before the barrier that ended k-step t-1)
     const int tl = t + STAGES - 1;
     const uint32_t st_l = lds0 + (tl % STAGES) * STAGE;
-    // One operand's refill goes out a sub-step after the other's: the
-    // activations (A) second in the forward layout (256x192 and 256x256
-    // tiles, contraction up to 8192), the weights (B) second in the
-    // input-gradient layout (256x192).  Measured on the ViT-22B layer: QKV
-    // forward 8%, MLP-up forward 2% and the out-projection forward and input
-    // gradient 5% faster; the forward with K = 24576 (MLP down) was 2% faster
-    // without it; later (two sub-steps) or both operands split in halves was
-    // slower.
-    constexpr bool kSpread = !AT && (BT ? BN == 192 : BN >= 192);
-    constexpr bool kALate = kSpread && !BT;
-    const bool spread = kSpread && (BT || p.K <= 8192);
     if (tl < nk) {
-      if (!kALate || !spread) la.issue(st_l, a_k0 + tl * a_step, wid);
-      if (!kSpread || kALate || !spread) lb.issue(st_l + A_BYTES, b_k0 + tl * b_step, wid);
+      la.issue(st_l, a_k0 + tl * a_step, wid);
+      lb.issue(st_l + A_BYTES, b_k0 + tl * b_step, wid);
     }
     const lds_char *As = smem + (t % STAGES) * STAGE;
 #pragma unroll
     for (int kk = 0; kk < KS; ++kk) {
       const int c = kk & 1, n = c ^ 1;
-      if constexpr (kSpread) {
-        if (kk == 1 && tl < nk && spread) {
-          if constexpr (kALate)
-            la.issue(st_l, a_k0 + tl * a_step, wid);
-          else
-            lb.issue(st_l + A_BYTES, b_k0 + tl * b_step, wid);
-        }
-      }
 #pragma unroll
       for (int i = 0; i < FM; ++i)
 #pragma unroll
-        for (int j = 0; j < FN; ++j) acc[i][j] = mfma32(bfr[c][j], af[c][i], acc[i][j]);
+        for (int j = 0; j < FN; ++j) acc[i][j] = mfma16(bfr[c][j], af[c][i], acc[i][j]);
       if constexpr (kDb) {
         if (do_db) {
 #pragma unroll
           for (int i = 0; i < FM; ++i) {
             const u32x4_t w = __builtin_bit_cast(u32x4_t, af[c][i]);
 #pragma unroll
-            for (int e = 0; e < 4; ++e) dbacc[i] += lo_bf(w[e]) + hi_bf(w[e]);
+            for (int e = 0; e < 4; ++e) dbacc[i] = add_pair(w[e], dbacc[i]);
           }
         }
       }
@@ -832,178 +805,17 @@ __global__ __launch_bounds__(WM *WN * 64, 1) void gemm_lds_kernel(GemmArgs p, ui
   store_tile_lds<EPI, BM, BN, WM, WN>(q, acc, m0, n0, wm, wn, lane, reinterpret_cast<float *>(smem_raw));
   if constexpr (kDb) {
     if (do_db) {
-      // lane l and l ^ 32 hold the two token halves of row (l % 32)
+      // the four 16-lane groups hold the token residues of row lane % 16
 #pragma unroll
       for (int i = 0; i < FM; ++i) {
-        const float tot = dbacc[i] + __shfl_xor(dbacc[i], 32, kWave);
-        const int row = m0 + wm * WTM + i * 32 + (lane & 31);
-        if (lane < 32 && row < q.M) q.db[row] = q.accumulate ? q.db[row] + tot : tot;
+        float tot = dbacc[i] + __shfl_xor(dbacc[i], 16, kWave);
+        tot += __shfl_xor(tot, 32, kWave);
+        const int row = m0 + wm * WTM + i * 16 + (lane & 15);
+        if (lane < 16 && row < q.M) q.db[row] = q.accumulate ? q.db[row] + tot : tot;
       }
     }
   }
 }
-
-// Variant of the two-stage kernel with uneven operand rings: the deep
-// operand (A when A_DEEP, else B) cycles through three LDS slots and is
-// refilled two stages ahead, the other through two slots, one stage ahead.
-// A 256x192x64 tile uses 3 x 32 + 2 x 24 KB = 144 KB (a 256x256 one would
-// take all 160 KB).  Each stage issues the shallow operand's next stage
-// first and the deep operand's stage a sub-step later, so the wait that ends
-// the stage leaves exactly the latter in flight; one barrier per stage as in
-// the two-stage kernel.  A stage's refill then has two stages of matrix work
-// to land in instead of one.
-
-template <int BM, int BN, int BK, int WM, int WN, bool A_DEEP, bool BT, Epi EPI>
-__global__ __launch_bounds__(WM *WN * 64, 1) void gemm_deep_kernel(GemmArgs p, uint32_t a_bytes, uint32_t b_bytes) {
-  constexpr int NW = WM * WN;
-  constexpr int WTM = BM / WM, WTN = BN / WN;
-  constexpr int FM = WTM / 32, FN = WTN / 32;
-  constexpr int KS = BK / 16;
-  using LA = DirectLoader<BM, BK, NW, false>;
-  using LB = DirectLoader<BN, BK, NW, BT>;
-  constexpr int A_BYTES = LA::BYTES, B_BYTES = LB::BYTES;
-  constexpr int SA = A_DEEP ? 3 : 2, SB = A_DEEP ? 2 : 3;
-  constexpr int B_BASE = SA * A_BYTES;
-  constexpr int NX = A_DEEP ? LA::NI : LB::NI;  // loads per wave of one stage of the deep operand
-  static_assert(KS % 2 == 0, "fragment double-buffering needs an even number of k-steps per stage");
-  extern __shared__ __attribute__((aligned(1024))) char smem_raw[];
-  const lds_char *smem = (const lds_char *)(smem_raw);
-
-  const int lane = threadIdx.x & 63;
-  const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int wm = wid / WN, wn = wid % WN;
-  const int tiles_m = (p.M + BM - 1) / BM, tiles_n = (p.N + BN - 1) / BN;
-  int tm, tn, kbeg, klen;
-  const int split = split_of(p, tiles_m, tiles_n, tm, tn, kbeg, klen);
-  const int m0 = tm * BM, n0 = tn * BN;
-
-  LA la;
-  LB lb;
-  la.init(p.A, a_bytes, p.lda, m0, wid, lane);
-  lb.init(p.B, b_bytes, p.ldb, n0, wid, lane);
-  const uint32_t a_k0 = static_cast<uint32_t>(kbeg) * 2;
-  const uint32_t b_step = BT ? static_cast<uint32_t>(BK) * p.ldb * 2 : BK * 2;
-  const uint32_t b_k0 = BT ? static_cast<uint32_t>(kbeg) * p.ldb * 2 : static_cast<uint32_t>(kbeg) * 2;
-  FragAddr<BM, BK, FM, false> fa;
-  FragAddr<BN, BK, FN, BT> fb;
-  fa.init(wm * WTM, lane);
-  fb.init(wn * WTN, lane);
-
-  f32x16_t acc[FM][FN];
-#pragma unroll
-  for (int i = 0; i < FM; ++i)
-#pragma unroll
-    for (int j = 0; j < FN; ++j) acc[i][j] = f32x16_t{};
-
-  const int nk = (klen + BK - 1) / BK;
-  const uint32_t lds0 = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(smem));
-  auto issue_a = [&](int t) { la.issue(lds0 + (t % SA) * A_BYTES, a_k0 + t * BK * 2, wid); };
-  auto issue_b = [&](int t) { lb.issue(lds0 + B_BASE + (t % SB) * B_BYTES, b_k0 + t * b_step, wid); };
-  auto issue_deep = [&](int t) {
-    if constexpr (A_DEEP)
-      issue_a(t);
-    else
-      issue_b(t);
-  };
-  auto issue_shallow = [&](int t) {
-    if constexpr (A_DEEP)
-      issue_b(t);
-    else
-      issue_a(t);
-  };
-  auto a_stage = [&](int t) { return smem + (t % SA) * A_BYTES; };
-  auto b_stage = [&](int t) { return smem + B_BASE + (t % SB) * B_BYTES; };
-
-  // stage 0 of both operands, then stage 1 of the deep one
-  issue_deep(0);
-  issue_shallow(0);
-  if (nk > 1) {
-    issue_deep(1);
-    wait_vmcnt<NX>();
-  } else {
-    wait_vmcnt<0>();
-  }
-  asm volatile("" ::: "memory");
-  __builtin_amdgcn_s_barrier();
-  asm volatile("" ::: "memory");
-
-  bf16x8_t af[2][FM], bfr[2][FN];
-#pragma unroll
-  for (int i = 0; i < FM; ++i) af[0][i] = fa.get(a_stage(0), i, 0);
-#pragma unroll
-  for (int j = 0; j < FN; ++j) bfr[0][j] = fb.get(b_stage(0), j, 0);
-
-  for (int t = 0; t < nk; ++t) {
-    // refill the slots stage t-1 used (every wave finished reading them
-    // before the barrier that ended stage t-1): shallow operand first
-    if (t + 1 < nk) issue_shallow(t + 1);
-    const lds_char *As = a_stage(t), *Bs = b_stage(t);
-#pragma unroll
-    for (int kk = 0; kk < KS; ++kk) {
-      const int c = kk & 1, n = c ^ 1;
-      // the deep operand has two stages of lead: its refill can go out a
-      // sub-step after the shallow one's
-      if (kk == 1 && t + 2 < nk) issue_deep(t + 2);
-#pragma unroll
-      for (int i = 0; i < FM; ++i)
-#pragma unroll
-        for (int j = 0; j < FN; ++j) acc[i][j] = mfma32(bfr[c][j], af[c][i], acc[i][j]);
-      if (kk + 1 < KS) {
-#pragma unroll
-        for (int i = 0; i < FM; ++i) af[n][i] = fa.get(As, i, kk + 1);
-#pragma unroll
-        for (int j = 0; j < FN; ++j) bfr[n][j] = fb.get(Bs, j, kk + 1);
-        interleave_reads<FM * FN, (FM + FN) * (BT ? 2 : 1)>();
-      } else if (t + 1 < nk) {
-        // stage t+1 of both operands landed for this wave (the deep
-        // operand's stage t+2, issued last, may stay in flight); this
-        // wave's LDS reads of stage t retired
-        if (t + 2 < nk)
-          wait_vmcnt<NX, 0>();
-        else
-          wait_vmcnt<0, 0>();
-        asm volatile("" ::: "memory");
-        __builtin_amdgcn_s_barrier();
-        asm volatile("" ::: "memory");
-#pragma unroll
-        for (int i = 0; i < FM; ++i) af[n][i] = fa.get(a_stage(t + 1), i, 0);
-#pragma unroll
-        for (int j = 0; j < FN; ++j) bfr[n][j] = fb.get(b_stage(t + 1), j, 0);
-      }
-    }
-  }
-  const GemmArgs q = split_outputs(p, split);
-  store_tile_lds<EPI, BM, BN, WM, WN>(q, acc, m0, n0, wm, wn, lane, reinterpret_cast<float *>(smem_raw));
-}
-
-template <int BM, int BN, int BK, int WM, int WN, bool A_DEEP, bool BT, Epi EPI>
-bool launch_deep_cfg(const GemmArgs &a, uint32_t a_bytes, uint32_t b_bytes, hipStream_t s) {
-  constexpr int NW = WM * WN;
-  constexpr size_t lds = static_cast<size_t>(A_DEEP ? 3 : 2) * DirectLoader<BM, BK, NW, false>::BYTES +
-                         static_cast<size_t>(A_DEEP ? 2 : 3) * DirectLoader<BN, BK, NW, BT>::BYTES;
-  static_assert(lds <= 160 * 1024, "LDS budget");
-  const int tiles = ((a.M + BM - 1) / BM) * ((a.N + BN - 1) / BN) * (a.splits > 1 ? a.splits : 1);
-  hipLaunchKernelGGL((gemm_deep_kernel<BM, BN, BK, WM, WN, A_DEEP, BT, EPI>), dim3(tiles), dim3(NW * 64), lds, s, a,
-                     a_bytes, b_bytes);
-  return true;
-}
-
-// 256x192 products that take the uneven-ring kernel (A deep): forward-layout
-// products with a contraction longer than kDeepFwdMinK.  Measured (same-box
-// A/B, ViT-22B layer): MLP-down forward (K = 24576) 543 -> 508 us; at
-// K = 6144 (QKV and out-projection forward) 1% slower than the two-stage
-// kernel, whose refill spread applies there; input gradients 0-8% slower
-// with A deep and equal to 8% slower with B deep, 256x256 forward tiles
-// 1-5% slower.  So only the forward layout with A deep is instantiated.
-constexpr int kDeepFwdMinK = 8192;
-
-// 256x192 input gradients with a contraction longer than this take the
-// ping-pong kernel.  Same-box A/B on the ViT-22B layer: alone, the MLP-up
-// input gradient (K = 24576) went 531 -> 523 us and the QKV one
-// (K = 18432) 402 -> 396 us; inside the layer chain the MLP-up one still
-// gained (541 -> 535 us) but the QKV one lost (401 -> 409 us), and at
-// K = 6144 (out-projection) it was no better.
-constexpr int kPpDgradMinK = 20480;
 
 template <int BM, int BN, int BK, int WM, int WN, int STAGES, bool AT, bool BT, Epi EPI>
 bool launch_lds_cfg(const GemmArgs &a, uint32_t a_bytes, uint32_t b_bytes, hipStream_t s) {
@@ -1036,80 +848,217 @@ bool launch_any(const GemmArgs &a, hipStream_t s) {
 }
 
 // ---------------------------------------------------------------------------
-// Ping-pong variant: 8 waves, two per SIMD (waves w and w + 4), in two groups
-// offset by one phase.  Each k-step has a load phase (issue this wave's share
-// of the DMA STAGES-1 k-steps ahead, read all of this k-step's fragments into
-// registers, wait for them) and a compute phase (the k-step's MFMAs, operands
-// already in registers); a workgroup barrier ends every phase.  While one
-// group computes, the other loads, so each SIMD's MFMA pipe is fed by one of
-// its two waves at a time.
+// Half-tile pipeline: 8 waves, two per SIMD (waves w and w + 4), in two groups
+// one slot apart, so that on every SIMD one wave issues MFMAs while the other
+// reads LDS and issues loads.  Each operand's k-step (64 wide) is two half
+// tiles: the first and the second half of every wave's rows.  A k-step is four
+// pairs of slots, one quadrant of the output each; X is the B half that is
+// already in registers, Y the other one:
+//   L0 reads A0          M0 = A0 x X
+//   L1 reads Y           M1 = A0 x Y
+//   L2 reads A1          M2 = A1 x Y
+//   L3 reads Y of t + 1  M3 = A1 x X     (X and Y swap from step to step)
+// A barrier ends every slot.  A wave's reads of an L slot retire in its M
+// slot (the MFMAs wait for them one by one, so the latency of the later reads
+// hides behind the earlier MFMAs), before the barrier that ends it.  Each L
+// slot also issues a load two k-steps ahead, into the half tile that was read
+// two L slots before: both groups' reads of it have retired by then.  A load
+// thus has 10 slots, 1.25 k-steps, before the wait that precedes its first
+// read, and up to 6 of the 8 half tiles in LDS are in flight.
 //
-// Buffer safety: k-step t is read by group 0 in phase 2t and by group 1 in
-// phase 2t+1; its buffer is refilled (k-step t+STAGES) from phase 2t+2 on.
-// Each wave waits for its own share of k-step t+1 in its load phase of t, so
-// both groups' shares have landed by the barrier that ends phase 2t+1.
+// What bounds it: with the loop free of vector instructions other than MFMAs
+// and LDS reads (addresses in registers, scalar load addressing) the matrix
+// cores are busy 97% of the k-loop's cycles, and the clock falls to what the
+// power budget allows.  So the fragments are 16x16x32: in a register-only loop
+// over random data they ran 2.04 PFLOP/s against 1.80 for 32x32x16.  With
+// transpose reads (strided operands) the LDS pipe's instruction rate binds
+// next: about 4.3 cycles each, 24 per wave and k-step for one strided operand,
+// 36 or 48 for two.  Measured on the ViT-22B layer (us, against the kernels
+// this replaced, on 32x32x16 with a whole k-step per barrier): QKV forward
+// 401 -> 342, out-projection forward 136 -> 118, MLP-up forward 548 -> 473,
+// MLP-down forward 532 -> 451, MLP-down input gradient 540 -> 478, MLP-up
+// 551 -> 511, QKV 417 -> 391, weight gradients 526 -> 513, 537 -> 520,
+// 410 -> 397.
 // ---------------------------------------------------------------------------
-template <int BM, int BN, int BK, int WM, int WN, int STAGES, bool AT, bool BT, Epi EPI>
-__global__ __launch_bounds__(WM *WN * 64, 1) void gemm_pp_kernel(GemmArgs p, uint32_t a_bytes, uint32_t b_bytes) {
-  constexpr int NW = WM * WN;
-  static_assert(NW == 8, "ping-pong needs two waves per SIMD");
-  constexpr int WTM = BM / WM, WTN = BN / WN;
-  constexpr int FM = WTM / 32, FN = WTN / 32;
-  constexpr int KS = BK / 16;
-  constexpr int A_BYTES = DirectLoader<BM, BK, NW, AT>::BYTES, B_BYTES = DirectLoader<BN, BK, NW, BT>::BYTES;
-  constexpr int STAGE = A_BYTES + B_BYTES;
-  static_assert(STAGES >= 3 && BK % 16 == 0, "pipeline shape");
+
+// One 1 KB wave load straight to LDS at base + OFF + 16 * lane.  M0 (the LDS
+// address) is left set: nothing else here reads it without setting it.
+template <int OFF>
+__device__ __forceinline__ void issue_lds16(const u32x4_t &rsrc, uint32_t base, uint32_t voff, uint32_t soff) {
+  asm volatile(
+      "s_add_u32 m0, %0, %4\n\t"
+      "s_nop 0\n\t"
+      "buffer_load_dwordx4 %1, %2, %3 offen lds"
+      :
+      : "s"(base), "v"(voff), "s"(rsrc), "s"(soff), "i"(OFF)
+      : "memory", "scc");
+}
+// The same for the lanes of `mask` only.
+template <int OFF>
+__device__ __forceinline__ void issue_lds16(const u32x4_t &rsrc, uint32_t base, uint32_t voff, uint32_t soff,
+                                            uint64_t mask) {
+  asm volatile(
+      "s_add_u32 m0, %0, %4\n\t"
+      "s_mov_b64 exec, %5\n\t"
+      "buffer_load_dwordx4 %1, %2, %3 offen lds\n\t"
+      "s_mov_b64 exec, -1"
+      :
+      : "s"(base), "v"(voff), "s"(rsrc), "s"(soff), "i"(OFF), "s"(mask)
+      : "memory", "scc");
+}
+
+// One operand's half tiles: NWV waves of 2 * FH fragments of 16 rows each;
+// half h holds each wave's fragments [h * FH, (h + 1) * FH).
+template <int NWV, int FH, bool TRANS>
+struct HalfTile {
+  static constexpr int BK = 64, KS = 2;                      // two 32-wide contraction steps
+  static constexpr int HR = FH * 16, WROWS = 2 * HR;         // rows per wave in a half, in the tile
+  static constexpr int ROWS = NWV * HR;                      // rows of a half tile
+  static constexpr int LROWS = TRANS ? 128 : ROWS;           // (transposed rows are padded)
+  static constexpr int BYTES = LROWS * BK * 2;               // LDS bytes of a half tile
+  static constexpr int WB = BYTES / 8;                       // per wave
+  static constexpr int NI = (WB + 1023) / 1024;              // loads per wave and half tile
+  static constexpr bool MASKED = ROWS != LROWS || WB % 1024 != 0;
+  static_assert(ROWS <= 128 && WB % 16 == 0, "half tile shape");
+  static constexpr int NOFF = TRANS ? FH : KS;
+  uint32_t voff[NI];
+  uint64_t mask[NI];
+  uint32_t half_off;
+  u32x4_t rsrc;
+  int off[NOFF];  // LDS offset of this wave's fragments in a half tile
+
+  __device__ __forceinline__ void init(const bf16_t *base, uint32_t nbytes, int ld, int r0, int w, int wid, int lane,
+                                       int lds_base) {
+    rsrc = make_rsrc(base, nbytes);
+    half_off = __builtin_amdgcn_readfirstlane(TRANS ? HR * 2 : static_cast<uint32_t>(HR) * ld * 2);
+#pragma unroll
+    for (int i = 0; i < NI; ++i) {
+      const int o = wid * WB + i * 1024 + lane * 16;
+      bool live = i * 1024 + lane * 16 < WB;
+      if constexpr (!TRANS) {
+        using T = NtTile<BK>;
+        const int br = o / T::RB, pch = (o % T::RB) >> 4;
+        const int c = pch ^ ((br / T::RP) % T::CPR);
+        const int r = br / HR * WROWS + br % HR;
+        voff[i] = static_cast<uint32_t>(((r0 + r) * static_cast<long>(ld) + c * 8) * 2);
+      } else {
+        const int k = o / (LROWS * 2), pch = (o % (LROWS * 2)) >> 4;
+        const int bc = (pch ^ t_swz(k)) * 8;
+        live = live && bc < ROWS;
+        const int c = bc / HR * WROWS + bc % HR;
+        voff[i] = static_cast<uint32_t>((k * static_cast<long>(ld) + r0 + c) * 2);
+      }
+      mask[i] = __ballot(live);
+    }
+    // fragment f of k-step kk: lane holds row lane % 16 of the fragment and
+    // contraction elements 8 * (lane / 16) .. + 7
+    if constexpr (!TRANS) {
+#pragma unroll
+      for (int kk = 0; kk < KS; ++kk)
+        off[kk] = lds_base + NtTile<BK>::off(w * HR + (lane & 15), kk * 4 + (lane >> 4));
+    } else {
+      const int k = 8 * (lane >> 4) + ((lane & 15) >> 2);
+#pragma unroll
+      for (int f = 0; f < FH; ++f) {
+        const int n = w * HR + f * 16 + 4 * (lane & 3);
+        off[f] = lds_base + k * (LROWS * 2) + (((n >> 3) ^ t_swz(k)) << 4) + (n & 7) * 2;
+      }
+    }
+    // addresses stay in registers: computed in the loop they would take issue
+    // slots from the other group's MFMAs
+#pragma unroll
+    for (int i = 0; i < NOFF; ++i) asm volatile("" : "+v"(off[i]));
+  }
+  template <int OFF>
+  __device__ __forceinline__ void issue(uint32_t wbase, uint32_t soff) const {
+    issue_one<OFF, 0>(wbase, soff);
+    if constexpr (NI > 1) issue_one<OFF, 1>(wbase, soff);
+  }
+  template <int OFF, int I>
+  __device__ __forceinline__ void issue_one(uint32_t wbase, uint32_t soff) const {
+    if constexpr (MASKED)
+      issue_lds16<OFF + I * 1024>(rsrc, wbase, voff[I], soff, mask[I]);
+    else
+      issue_lds16<OFF + I * 1024>(rsrc, wbase, voff[I], soff);
+  }
+  __device__ __forceinline__ bf16x8_t get(const lds_char *half, int f, int kk) const {
+    if constexpr (!TRANS) {
+      return *reinterpret_cast<const __attribute__((address_space(3))) bf16x8_t *>(half + off[kk] + f * 16 * BK * 2);
+    } else {
+      const lds_char *q = half + off[f] + kk * 32 * LROWS * 2;
+      return lds_read_tr(q, q + 4 * LROWS * 2);
+    }
+  }
+};
+
+template <int N>
+using cnt = std::integral_constant<int, N>;
+
+template <int WM, int WN, int FMH, int FNH, bool AT, bool BT, Epi EPI>
+__global__ __launch_bounds__(512, 1) void gemm_half_kernel(GemmArgs p, uint32_t a_bytes, uint32_t b_bytes) {
+  static_assert(WM * WN == 8, "eight waves, two per SIMD");
+  constexpr int BM = WM * FMH * 32, BN = WN * FNH * 32, BK = 64, KS = 2;
+  constexpr int WTM = BM / WM, FM = 2 * FMH, FN = 2 * FNH;
+  using TA = HalfTile<WM, FMH, AT>;
+  using TB = HalfTile<WN, FNH, BT>;
+  constexpr int NA = TA::NI, NB = TB::NI;
+  // LDS: [A: stage 0 half 0, half 1, stage 1 half 0, half 1] [B: the same]
+  constexpr int B_BASE = 4 * TA::BYTES;
+  // A fragments read one L slot early when A takes transpose reads (twice the
+  // LDS instructions): evens the L slots out
+  constexpr int PRE = AT ? FMH / 2 : 0;
   extern __shared__ __attribute__((aligned(1024))) char smem_raw[];
-  const lds_char *smem = (const lds_char *)(smem_raw);  // generic -> LDS address space
+  const lds_char *smem = (const lds_char *)(smem_raw);
 
   const int lane = threadIdx.x & 63;
-  const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // wave-uniform
-  const int grp = wid >> 2;                                          // 0: waves 0-3, 1: waves 4-7
+  const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int grp = wid >> 2;
   const int wm = wid / WN, wn = wid % WN;
   const int tiles_m = (p.M + BM - 1) / BM, tiles_n = (p.N + BN - 1) / BN;
   int tm, tn, kbeg, klen;
   const int split = split_of(p, tiles_m, tiles_n, tm, tn, kbeg, klen);
   const int m0 = tm * BM, n0 = tn * BN;
 
-  DirectLoader<BM, BK, NW, AT> la;
-  DirectLoader<BN, BK, NW, BT> lb;
-  la.init(p.A, a_bytes, p.lda, m0, wid, lane);
-  lb.init(p.B, b_bytes, p.ldb, n0, wid, lane);
+  TA la;
+  TB lb;
+  const uint32_t lds0 = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(smem));
+  la.init(p.A, a_bytes, p.lda, m0, wm, wid, lane, 0);
+  lb.init(p.B, b_bytes, p.ldb, n0, wn, wid, lane, B_BASE);
   const uint32_t a_step = AT ? static_cast<uint32_t>(BK) * p.lda * 2 : BK * 2;
   const uint32_t b_step = BT ? static_cast<uint32_t>(BK) * p.ldb * 2 : BK * 2;
-  const uint32_t a_k0 = AT ? static_cast<uint32_t>(kbeg) * p.lda * 2 : static_cast<uint32_t>(kbeg) * 2;
-  const uint32_t b_k0 = BT ? static_cast<uint32_t>(kbeg) * p.ldb * 2 : static_cast<uint32_t>(kbeg) * 2;
-  FragAddr<BM, BK, FM, AT> fa;
-  FragAddr<BN, BK, FN, BT> fb;
-  fa.init(wm * WTM, lane);
-  fb.init(wn * WTN, lane);
+  // byte offsets of the k-step whose loads are issued next
+  uint32_t so_a = AT ? static_cast<uint32_t>(kbeg) * p.lda * 2 : static_cast<uint32_t>(kbeg) * 2;
+  uint32_t so_b = BT ? static_cast<uint32_t>(kbeg) * p.ldb * 2 : static_cast<uint32_t>(kbeg) * 2;
+  const uint32_t wa = __builtin_amdgcn_readfirstlane(lds0 + wid * TA::WB);
+  const uint32_t wb = __builtin_amdgcn_readfirstlane(lds0 + B_BASE + wid * TB::WB);
 
-  f32x16_t acc[FM][FN];
+  f32x4_t acc[FM][FN];
 #pragma unroll
   for (int i = 0; i < FM; ++i)
 #pragma unroll
-    for (int j = 0; j < FN; ++j) acc[i][j] = f32x16_t{};
-  constexpr bool kDb = (EPI == Epi::kF32);
-  const bool do_db = kDb && p.db != nullptr && tn == 0 && wn == 0;
-  float dbacc[FM];
+    for (int j = 0; j < FN; ++j) acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+  // Weight gradient: the bias gradient db[m] = sum_k A(m, k), summed from the
+  // A fragments in registers by the first column tile's workgroups; each wave
+  // column takes the fragments i % WN == wn of a half (fixed order:
+  // deterministic).
+  constexpr bool kDb = (EPI == Epi::kF32) && AT;
+  constexpr int DBF = (FMH + WN - 1) / WN;
+  const bool do_db = kDb && p.db != nullptr && tn == 0;
+  float dbacc[2][DBF];
 #pragma unroll
-  for (int i = 0; i < FM; ++i) dbacc[i] = 0.f;
+  for (int h = 0; h < 2; ++h)
+#pragma unroll
+    for (int i = 0; i < DBF; ++i) dbacc[h][i] = 0.f;
 
   const int nk = (klen + BK - 1) / BK;
-  const uint32_t lds0 = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(smem));
-  constexpr int PER_STAGE = DirectLoader<BM, BK, NW, AT>::NI + DirectLoader<BN, BK, NW, BT>::NI;
-#pragma unroll
-  for (int s = 0; s < STAGES - 1; ++s) {
-    if (s < nk) {
-      la.issue(lds0 + s * STAGE, a_k0 + s * a_step, wid);
-      lb.issue(lds0 + s * STAGE + A_BYTES, b_k0 + s * b_step, wid);
-    }
-  }
-  // k-step 0 resident for every wave
-  if (STAGES - 1 < nk)
-    wait_vmcnt<PER_STAGE * (STAGES - 2)>();
-  else
-    wait_vmcnt<0>();
+  constexpr std::integral_constant<int, 0> c0{};
+  constexpr std::integral_constant<int, 1> c1{};
+  auto issue_a = [&](auto st, auto h) {
+    la.template issue<(st.value * 2 + h.value) * TA::BYTES>(wa, so_a + (h.value ? la.half_off : 0u));
+  };
+  auto issue_b = [&](auto st, auto h) {
+    lb.template issue<(st.value * 2 + h.value) * TB::BYTES>(wb, so_b + (h.value ? lb.half_off : 0u));
+  };
   auto barrier = [] {
     __builtin_amdgcn_sched_barrier(0);
     asm volatile("" ::: "memory");
@@ -1117,51 +1066,151 @@ __global__ __launch_bounds__(WM *WN * 64, 1) void gemm_pp_kernel(GemmArgs p, uin
     asm volatile("" ::: "memory");
     __builtin_amdgcn_sched_barrier(0);
   };
-  barrier();
-  if (grp == 1) barrier();  // group 1 runs one phase behind
 
-  bf16x8_t af[KS][FM], bfr[KS][FN];
-  for (int t = 0; t < nk; ++t) {
-    // ---- load phase
-    const int tl = t + STAGES - 1;
-    if (tl < nk) {
-      const uint32_t st = lds0 + (tl % STAGES) * STAGE;
-      la.issue(st, a_k0 + tl * a_step, wid);
-      lb.issue(st + A_BYTES, b_k0 + tl * b_step, wid);
+  bf16x8_t a[KS][FMH], b0[KS][FNH], b1[KS][FNH], pre[2][PRE > 0 ? PRE : 1];
+  auto read_pre = [&](auto st, auto h) {
+    if constexpr (PRE > 0) {
+#pragma unroll
+      for (int i = 0; i < PRE; ++i) pre[h.value][i] = la.get(smem + (st.value * 2 + h.value) * TA::BYTES, i, 0);
     }
-    const lds_char *As = smem + (t % STAGES) * STAGE;
+  };
+  auto read_a = [&](auto st, auto h) {
 #pragma unroll
-    for (int kk = 0; kk < KS; ++kk) {
+    for (int kk = 0; kk < KS; ++kk)
 #pragma unroll
-      for (int i = 0; i < FM; ++i) af[kk][i] = fa.get(As, i, kk);
+      for (int i = 0; i < FMH; ++i)
+        if (kk > 0 || i >= PRE) a[kk][i] = la.get(smem + (st.value * 2 + h.value) * TA::BYTES, i, kk);
+  };
+  auto read_b = [&](auto st, auto h) {
 #pragma unroll
-      for (int j = 0; j < FN; ++j) bfr[kk][j] = fb.get(As + A_BYTES, j, kk);
-    }
-    // own share of k-step t+1 landed (k-steps t+2.. may still be in flight)
-    if (t + STAGES - 1 < nk)
-      wait_vmcnt<PER_STAGE * (STAGES - 2), 0>();
-    else
-      wait_vmcnt<0, 0>();
-    barrier();
-    // ---- compute phase
+    for (int kk = 0; kk < KS; ++kk)
 #pragma unroll
-    for (int kk = 0; kk < KS; ++kk) {
+      for (int j = 0; j < FNH; ++j)
+        (h.value ? b1 : b0)[kk][j] = lb.get(smem + (st.value * 2 + h.value) * TB::BYTES, j, kk);
+  };
+  // one quadrant; SUM: also add this A half's rows into the bias gradient
+  auto mma = [&](auto ahc, auto bhc, auto sum) {
+    constexpr int ah = decltype(ahc)::value, bh = decltype(bhc)::value;
+    auto fa = [&](int kk, int i) { return (kk == 0 && i < PRE) ? pre[ah][i < PRE ? i : 0] : a[kk][i]; };
 #pragma unroll
-      for (int i = 0; i < FM; ++i)
+    for (int kk = 0; kk < KS; ++kk)
 #pragma unroll
-        for (int j = 0; j < FN; ++j) acc[i][j] = mfma32(bfr[kk][j], af[kk][i], acc[i][j]);
-      if constexpr (kDb) {
-        if (do_db) {
+      for (int i = 0; i < FMH; ++i)
 #pragma unroll
-          for (int i = 0; i < FM; ++i) {
-            const u32x4_t w = __builtin_bit_cast(u32x4_t, af[kk][i]);
+        for (int j = 0; j < FNH; ++j)
+          acc[ah * FMH + i][bh * FNH + j] =
+              mfma16((bh ? b1 : b0)[kk][j], fa(kk, i), acc[ah * FMH + i][bh * FNH + j]);
+    wait_vmcnt<63, 0>();  // this slot's reads retired before the barrier (the data was used above)
+    if constexpr (decltype(sum)::value) {
 #pragma unroll
-            for (int e = 0; e < 4; ++e) dbacc[i] += lo_bf(w[e]) + hi_bf(w[e]);
-          }
+      for (int i = 0; i < FMH; ++i) {
+        if (i % WN != wn) continue;
+#pragma unroll
+        for (int kk = 0; kk < KS; ++kk) {
+          const u32x4_t w = __builtin_bit_cast(u32x4_t, fa(kk, i));
+#pragma unroll
+          for (int e = 0; e < 4; ++e) dbacc[ah][i / WN] = add_pair(w[e], dbacc[ah][i / WN]);
         }
       }
     }
+  };
+
+  // k-steps 0 and 1, in the order the loop reads them (X of step 0 is B0, of
+  // step 1 B1)
+  issue_b(c0, c0);
+  issue_a(c0, c0);
+  issue_b(c0, c1);
+  issue_a(c0, c1);
+  so_a += a_step;
+  so_b += b_step;
+  if (nk > 1) {
+    issue_b(c1, c1);
+    issue_a(c1, c0);
+    issue_b(c1, c0);
+    so_b += b_step;
+    wait_vmcnt<2 * NA + 3 * NB>();
+  } else {
+    wait_vmcnt<NA + NB>();
+  }
+  barrier();
+  read_b(c0, c0);
+  read_pre(c0, c0);
+  wait_vmcnt<63, 0>();
+  barrier();
+  if (grp == 1) barrier();  // group 1 runs one slot behind
+
+  // Waits of the steady state (both k-steps t + 1 and t + 2 exist), of the
+  // last but one k-step and of the last: each leaves in flight exactly the
+  // loads younger than what the next L slot reads.
+  auto wait3 = [](bool more2, bool more1, auto n2, auto n1, auto n0) {
+    if (more2)
+      wait_vmcnt<n2.value>();
+    else if (more1)
+      wait_vmcnt<n1.value>();
+    else
+      wait_vmcnt<n0.value>();
+  };
+  // One k-step in stage st.  FULL: k-steps t + 1 and t + 2 exist.
+  auto step = [&](auto st, auto full, auto db, int t) {
+    constexpr bool FULL = decltype(full)::value;
+    constexpr std::integral_constant<int, st.value> X{};
+    constexpr std::integral_constant<int, 1 - st.value> Y{};
+    constexpr int PA = PRE > 0 ? NA : 0;  // (the early reads need A one slot sooner)
+    const bool more2 = FULL || t + 2 < nk, more1 = FULL || t + 1 < nk;
+    // ---- L0, M0
+    if (more1) issue_a(Y, c1);
+    so_a += a_step;
+    read_a(st, c0);
+    wait3(more2, more1, cnt<3 * NA + 2 * NB - PA>(), cnt<3 * NA + 2 * NB - PA>(), cnt<NA - PA>());
     barrier();
+    mma(c0, X, db);
+    barrier();
+    // ---- L1, M1
+    if (more2) issue_b(st, X);
+    read_b(st, Y);
+    read_pre(st, c1);
+    wait3(more2, more1, cnt<2 * NA + 3 * NB>(), cnt<2 * (NA + NB)>(), c0);
+    barrier();
+    mma(c0, Y, c0);
+    barrier();
+    // ---- L2, M2
+    if (more2) issue_a(st, c0);
+    read_a(st, c1);
+    wait3(more2, more1, cnt<3 * NA + 2 * NB - PA>(), cnt<2 * NA + NB - PA>(), c0);
+    barrier();
+    mma(c1, Y, db);
+    barrier();
+    // ---- L3, M3 (after the last k-step the reads return stale data, unused)
+    if (more2) issue_b(st, Y);
+    read_b(Y, Y);
+    read_pre(Y, c0);
+    wait3(more2, more1, cnt<2 * NA + 3 * NB>(), cnt<NA + NB>(), c0);
+    barrier();
+    mma(c1, X, c0);
+    so_b += b_step;
+    barrier();
+  };
+  auto k_loop = [&](auto db) {
+    int t = 0;
+    for (; t + 3 < nk; t += 2) {
+      step(c0, c1, db, t);
+      step(c1, c1, db, t + 1);
+    }
+    for (;;) {
+      step(c0, c0, db, t);
+      if (++t >= nk) break;
+      step(c1, c0, db, t);
+      if (++t >= nk) break;
+    }
+  };
+  if constexpr (kDb) {
+    // two copies of the loop: a test of do_db inside it costs every workgroup
+    if (do_db)
+      k_loop(c1);
+    else
+      k_loop(c0);
+  } else {
+    k_loop(c0);
   }
   if (grp == 0) barrier();  // match group 1's extra barrier
 
@@ -1170,40 +1219,38 @@ __global__ __launch_bounds__(WM *WN * 64, 1) void gemm_pp_kernel(GemmArgs p, uin
   if constexpr (kDb) {
     if (do_db) {
 #pragma unroll
-      for (int i = 0; i < FM; ++i) {
-        const float tot = dbacc[i] + __shfl_xor(dbacc[i], 32, kWave);
-        const int row = m0 + wm * WTM + i * 32 + (lane & 31);
-        if (lane < 32 && row < q.M) q.db[row] = q.accumulate ? q.db[row] + tot : tot;
-      }
+      for (int h = 0; h < 2; ++h)
+#pragma unroll
+        for (int i = 0; i < DBF; ++i) {
+          // the four 16-lane groups hold the k residues of row lane % 16
+          float tot = dbacc[h][i] + __shfl_xor(dbacc[h][i], 16, kWave);
+          tot += __shfl_xor(tot, 32, kWave);
+          const int f = i * WN + wn;
+          const int row = m0 + wm * WTM + (h * FMH + f) * 16 + (lane & 15);
+          if (f < FMH && lane < 16 && row < q.M) q.db[row] = q.accumulate ? q.db[row] + tot : tot;
+        }
     }
   }
 }
 
-template <int BM, int BN, int BK, int WM, int WN, int STAGES, bool AT, bool BT, Epi EPI>
-bool launch_pp_cfg(const GemmArgs &a, uint32_t a_bytes, uint32_t b_bytes, hipStream_t s) {
-  constexpr int NW = WM * WN;
-  constexpr size_t lds = static_cast<size_t>(STAGES) *
-                         (DirectLoader<BM, BK, NW, AT>::BYTES + DirectLoader<BN, BK, NW, BT>::BYTES);
+template <int WM, int WN, int FMH, int FNH, bool AT, bool BT, Epi EPI>
+bool launch_half_cfg(const GemmArgs &a, uint32_t a_bytes, uint32_t b_bytes, hipStream_t s) {
+  constexpr int BM = WM * FMH * 32, BN = WN * FNH * 32;
+  constexpr size_t pipe = 4 * (HalfTile<WM, FMH, AT>::BYTES + HalfTile<WN, FNH, BT>::BYTES);
+  constexpr size_t epi = static_cast<size_t>(kEpiRows) * (BN + 4) * sizeof(float);
+  constexpr size_t lds = pipe > epi ? pipe : epi;
   static_assert(lds <= 160 * 1024, "LDS budget");
   const int tiles = ((a.M + BM - 1) / BM) * ((a.N + BN - 1) / BN) * (a.splits > 1 ? a.splits : 1);
-  hipLaunchKernelGGL((gemm_pp_kernel<BM, BN, BK, WM, WN, STAGES, AT, BT, EPI>), dim3(tiles), dim3(NW * 64), lds, s, a,
-                     a_bytes, b_bytes);
+  hipLaunchKernelGGL((gemm_half_kernel<WM, WN, FMH, FNH, AT, BT, EPI>), dim3(tiles), dim3(512), lds, s, a, a_bytes,
+                     b_bytes);
   return true;
 }
 
 // Direct-to-LDS path: pick the tile that minimises (rounds of 256 CUs) x
-// (tile area / per-tile efficiency).  Measured on MI355X at the ViT-22B layer
-// shapes with random bf16 data: 256x256 tiles are the most efficient per
+// (tile area / per-tile efficiency).  256x256 tiles are the most efficient per
 // tile, 256x192 tiles divide the 6144- and 18432-wide outputs into whole
-// rounds, 128x128 tiles serve small problems.  Kernel per tile and layout:
-//   tile      forward (A, B k-contiguous)  input gradient (B strided)  weight gradient (both strided)
-//   256x256   gemm_lds_kernel BK64 2-stage  gemm_pp_kernel BK32 4-stage  gemm_pp_kernel BK32 4-stage
-//   256x192   gemm_lds_kernel BK64 2-stage  gemm_lds_kernel BK64 2-stage  gemm_pp_kernel BK32 4-stage
-//             (K > 8192: gemm_deep_kernel)  (K > 20480: gemm_pp_kernel)
-//   128x128   gemm_lds_kernel BK64 2-stage  gemm_lds_kernel BK64 2-stage  gemm_lds_kernel BK64 2-stage
-// The ping-pong schedule hides the transpose reads of strided operands
-// better where it is used; on the 256x192 input gradients it helps only with
-// long contractions.
+// rounds; both run gemm_half_kernel.  128x128 tiles serve small problems
+// (gemm_lds_kernel, BK 64, two stages, two workgroups per CU).
 // Returns false when the operands do not fit the path's constraints.
 template <bool AT, bool BT, Epi EPI>
 bool launch_lds(const GemmArgs &a, hipStream_t s, TileShape t) {
@@ -1212,22 +1259,8 @@ bool launch_lds(const GemmArgs &a, hipStream_t s, TileShape t) {
   // operand extents (bytes) bound the buffer loads
   const uint32_t ab = static_cast<uint32_t>(static_cast<uint64_t>(AT ? a.K : a.M) * a.lda * 2);
   const uint32_t bb = static_cast<uint32_t>(static_cast<uint64_t>(BT ? a.K : a.N) * a.ldb * 2);
-  if (t.bm == 256 && t.bn == 256) {
-    if constexpr (BT) return launch_pp_cfg<256, 256, 32, 2, 4, 4, AT, BT, EPI>(a, ab, bb, s);
-    return launch_lds_cfg<256, 256, BK, 2, 4, 2, AT, BT, EPI>(a, ab, bb, s);
-  }
-  if (t.bm == 256 && t.bn == 192) {
-    if constexpr (AT && BT) return launch_pp_cfg<256, 192, 32, 4, 2, 4, AT, BT, EPI>(a, ab, bb, s);
-    if constexpr (!AT && BT) {
-      if (a.K > kPpDgradMinK) return launch_pp_cfg<256, 192, 32, 4, 2, 4, AT, BT, EPI>(a, ab, bb, s);
-    }
-    if constexpr (!AT && !BT) {
-      if (a.K > kDeepFwdMinK) return launch_deep_cfg<256, 192, BK, 4, 2, true, false, EPI>(a, ab, bb, s);
-    }
-    return launch_lds_cfg<256, 192, BK, 4, 2, 2, AT, BT, EPI>(a, ab, bb, s);
-  }
-  if (t.bm == 256) return launch_lds_cfg<256, 128, BK, 4, 2, 2, AT, BT, EPI>(a, ab, bb, s);
-  if (t.bn == 256) return launch_lds_cfg<128, 256, BK, 2, 4, 2, AT, BT, EPI>(a, ab, bb, s);
+  if (t.bm == 256 && t.bn == 256) return launch_half_cfg<2, 4, 4, 2, AT, BT, EPI>(a, ab, bb, s);
+  if (t.bm == 256) return launch_half_cfg<4, 2, 2, 3, AT, BT, EPI>(a, ab, bb, s);
   return launch_lds_cfg<128, 128, BK, 2, 2, 2, AT, BT, EPI>(a, ab, bb, s);
 }
 
