@@ -133,11 +133,11 @@ def _split_item(pid, nb, tiles_m, tiles_n):
 def fetch_floor(rows, cols, K, bm, bn, splits):
     """Operand bytes the eight L2s must fetch at least for one GEMM launch
     (output rows x cols, contraction K, bf16 operands): the workgroups of a
-    round run together (one per CU, two for 128x128 tiles), the eighth of
+    round run together (one per CU, two for the tiles that share one), the eighth of
     them on one XCD share its L2, and an operand panel (a tile row's or tile
     column's slice of the contraction) outlives neither its round nor its
     XCD.  Each round's distinct panels per XCD, summed."""
-    per_round = 512 if (bm, bn) == (128, 128) else 256
+    per_round = 512 if (bm, bn) in ((192, 128), (128, 128), (64, 128), (64, 64)) else 256
     tm, tn = -(-rows // bm), -(-cols // bn)
     nb = tm * tn * splits
     kc = -(-K // splits) if splits > 1 else K

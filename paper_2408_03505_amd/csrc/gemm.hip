@@ -27,6 +27,7 @@
 // groups of row tiles, which keeps the operand panels it shares in its L2.
 #include <algorithm>
 #include <type_traits>
+#include <utility>
 
 #include "common.hpp"
 #include "kernels.hpp"
@@ -563,272 +564,6 @@ struct NtTile {
 // 12..15) go to eight disjoint 32-byte ranges.
 __device__ __forceinline__ int t_swz(int k) { return ((k & 3) << 1) | (((k >> 3) & 1) << 3); }
 
-template <int ROWS>
-struct TTile {
-  static constexpr int TROWS = ROWS <= 128 ? 128 : 256;  // padded k-row length
-  static_assert(ROWS <= 256 && ROWS % 16 == 0, "transposed tile width");
-  __device__ static __forceinline__ int off(int k, int j) { return k * (TROWS * 2) + ((j ^ t_swz(k)) << 4); }
-};
-
-template <int ROWS, int BK, int NW, bool TRANS>
-struct DirectLoader {
-  // LDS bytes of one stage of this operand (transposed tiles are padded)
-  static constexpr int BYTES = TRANS ? TTile<ROWS>::TROWS * BK * 2 : ROWS * BK * 2;
-  static constexpr int NI = BYTES / (1024 * NW);
-  static_assert(BYTES % (1024 * NW) == 0, "tile bytes must split into whole wave loads");
-  uint32_t voff[NI];
-  uint32_t live;  // bit i: this lane's chunk of load i is real data (not padding)
-  u32x4_t rsrc;
-
-  // base/nbytes: the operand tensor; ld its leading dimension (elements);
-  // r0 the first tile row (output row of this operand).
-  __device__ __forceinline__ void init(const bf16_t *base, uint32_t nbytes, int ld, int r0, int wid, int lane) {
-    rsrc = make_rsrc(base, nbytes);
-    live = 0;
-#pragma unroll
-    for (int i = 0; i < NI; ++i) {
-      const int o = (wid * NI + i) * 1024 + lane * 16;
-      if constexpr (!TRANS) {
-        using T = NtTile<BK>;
-        const int r = o / T::RB, pch = (o % T::RB) >> 4;
-        const int c = pch ^ ((r / T::RP) % T::CPR);
-        voff[i] = static_cast<uint32_t>(((r0 + r) * static_cast<long>(ld) + c * 8) * 2);
-        live |= 1u << i;
-      } else {
-        constexpr int TR = TTile<ROWS>::TROWS;
-        const int k = o / (TR * 2), pch = (o % (TR * 2)) >> 4;
-        const int j = pch ^ t_swz(k);
-        voff[i] = static_cast<uint32_t>((k * static_cast<long>(ld) + r0 + j * 8) * 2);
-        if (j * 8 < ROWS) live |= 1u << i;
-      }
-    }
-  }
-  // Enqueue this wave's share of one stage: soff is the k-step's byte offset.
-  __device__ __forceinline__ void issue(uint32_t tile_addr, uint32_t soff, int wid) {
-#pragma unroll
-    for (int i = 0; i < NI; ++i) {
-      const uint32_t dst = __builtin_amdgcn_readfirstlane(tile_addr + static_cast<uint32_t>((wid * NI + i) * 1024));
-      const uint32_t so = __builtin_amdgcn_readfirstlane(soff);
-      if (!TRANS || TTile<ROWS>::TROWS == ROWS || ((live >> i) & 1u)) buffer_load_lds16(rsrc, dst, voff[i], so);
-    }
-  }
-};
-
-// Per-lane LDS byte offsets of one operand's 16x16x32 MFMA fragments
-// (stage-relative): the lane holds row lane % 16 of the fragment and
-// contraction elements 8 * (lane / 16) .. + 7 of a 32-wide step.
-template <int ROWS, int BK, int F, bool TRANS>
-struct FragAddr {
-  static constexpr int KS = BK / 32;
-  // non-transposed: one address per k-step (fragments add 16 rows);
-  // transposed: one per fragment (k-steps add 32 k-rows, the second half of
-  // the eight elements 4 k-rows).
-  static constexpr int N = TRANS ? F : KS;
-  int off[N];
-  __device__ __forceinline__ void init(int rbase, int lane) {
-    if constexpr (!TRANS) {
-#pragma unroll
-      for (int kk = 0; kk < KS; ++kk) off[kk] = NtTile<BK>::off(rbase + (lane & 15), kk * 4 + (lane >> 4));
-    } else {
-      const int k = 8 * (lane >> 4) + ((lane & 15) >> 2);
-#pragma unroll
-      for (int f = 0; f < F; ++f) {
-        const int n = rbase + f * 16 + 4 * (lane & 3);
-        off[f] = TTile<ROWS>::off(k, n >> 3) + (n & 7) * 2;
-      }
-    }
-  }
-  __device__ __forceinline__ bf16x8_t get(const lds_char *tile, int f, int kk) const {
-    if constexpr (!TRANS) {
-      return *reinterpret_cast<const __attribute__((address_space(3))) bf16x8_t *>(tile + off[kk] +
-                                                                                     f * 16 * BK * 2);
-    } else {
-      constexpr int TR = TTile<ROWS>::TROWS;
-      const lds_char *q = tile + off[f] + kk * 32 * TR * 2;
-      return lds_read_tr(q, q + 4 * TR * 2);
-    }
-  }
-};
-
-// Scheduling hint for one k-step: spread the NR LDS reads of the next
-// k-step's fragments evenly between the NM MFMAs of this k-step, so that the
-// reads have a whole k-step of MFMA work to land in.
-template <int NM, int NR, int M = 0>
-__device__ __forceinline__ void interleave_reads() {
-  if constexpr (M < NM) {
-    constexpr int per = (NR + NM - 1) / NM;
-    constexpr int done = M * per < NR ? M * per : NR;
-    constexpr int r = (NR - done) < per ? (NR - done) : per;
-    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);  // one MFMA
-    if constexpr (r > 0) __builtin_amdgcn_sched_group_barrier(0x100, r, 0);  // then r LDS reads
-    interleave_reads<NM, NR, M + 1>();
-  }
-}
-
-template <int BM, int BN, int BK, int WM, int WN, int STAGES, bool AT, bool BT, Epi EPI>
-__global__ __launch_bounds__(WM *WN * 64, 1) void gemm_lds_kernel(GemmArgs p, uint32_t a_bytes, uint32_t b_bytes) {
-  constexpr int NW = WM * WN;
-  constexpr int WTM = BM / WM, WTN = BN / WN;
-  constexpr int FM = WTM / 16, FN = WTN / 16;
-  constexpr int KS = BK / 32;
-  constexpr int A_BYTES = DirectLoader<BM, BK, NW, AT>::BYTES, B_BYTES = DirectLoader<BN, BK, NW, BT>::BYTES;
-  constexpr int STAGE = A_BYTES + B_BYTES;
-  static_assert(STAGES >= 2 && BK % 32 == 0, "pipeline shape");
-  extern __shared__ __attribute__((aligned(1024))) char smem_raw[];
-  const lds_char *smem = (const lds_char *)(smem_raw);  // generic -> LDS address space
-
-  const int lane = threadIdx.x & 63;
-  const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // wave-uniform
-  const int wm = wid / WN, wn = wid % WN;
-  const int tiles_m = (p.M + BM - 1) / BM, tiles_n = (p.N + BN - 1) / BN;
-  int tm, tn, kbeg, klen;
-  const int split = split_of(p, tiles_m, tiles_n, tm, tn, kbeg, klen);
-  const int m0 = tm * BM, n0 = tn * BN;
-
-  DirectLoader<BM, BK, NW, AT> la;
-  DirectLoader<BN, BK, NW, BT> lb;
-  la.init(p.A, a_bytes, p.lda, m0, wid, lane);
-  lb.init(p.B, b_bytes, p.ldb, n0, wid, lane);
-  // byte step of one k-step along each operand, and of the split's first k
-  const uint32_t a_step = AT ? static_cast<uint32_t>(BK) * p.lda * 2 : BK * 2;
-  const uint32_t b_step = BT ? static_cast<uint32_t>(BK) * p.ldb * 2 : BK * 2;
-  const uint32_t a_k0 = AT ? static_cast<uint32_t>(kbeg) * p.lda * 2 : static_cast<uint32_t>(kbeg) * 2;
-  const uint32_t b_k0 = BT ? static_cast<uint32_t>(kbeg) * p.ldb * 2 : static_cast<uint32_t>(kbeg) * 2;
-
-  FragAddr<BM, BK, FM, AT> fa;
-  FragAddr<BN, BK, FN, BT> fb;
-  fa.init(wm * WTM, lane);
-  fb.init(wn * WTN, lane);
-
-  f32x4_t acc[FM][FN];
-#pragma unroll
-  for (int i = 0; i < FM; ++i)
-#pragma unroll
-    for (int j = 0; j < FN; ++j) acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-
-  // Weight gradient: the bias gradient db[m] = sum_k A(m, k) is summed from
-  // the A fragments already in registers by the first wave column of the
-  // first column tile (fixed order: deterministic).
-  constexpr bool kDb = (EPI == Epi::kF32);
-  const bool do_db = kDb && p.db != nullptr && tn == 0 && wn == 0;
-  float dbacc[FM];
-#pragma unroll
-  for (int i = 0; i < FM; ++i) dbacc[i] = 0.f;
-
-  const int nk = (klen + BK - 1) / BK;
-  const uint32_t lds0 = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(smem));
-  constexpr int PER_STAGE = DirectLoader<BM, BK, NW, AT>::NI + DirectLoader<BN, BK, NW, BT>::NI;
-#pragma unroll
-  for (int s = 0; s < STAGES - 1; ++s) {
-    if (s < nk) {
-      la.issue(lds0 + s * STAGE, a_k0 + s * a_step, wid);
-      lb.issue(lds0 + s * STAGE + A_BYTES, b_k0 + s * b_step, wid);
-    }
-  }
-  // k-step 0 resident for every wave
-  if (STAGES - 1 < nk)
-    wait_vmcnt<PER_STAGE * (STAGES - 2)>();
-  else
-    wait_vmcnt<0>();
-  asm volatile("" ::: "memory");
-  __builtin_amdgcn_s_barrier();
-  asm volatile("" ::: "memory");
-
-  // Fragments are double-buffered in registers: the next k-step's LDS reads
-  // are issued behind the current k-step's MFMAs.  The stage barrier sits
-  // after the last k-step's MFMAs are issued, so their execution covers the
-  // barrier and the first reads of the next stage.
-  bf16x8_t af[2][FM], bfr[2][FN];
-#pragma unroll
-  for (int i = 0; i < FM; ++i) af[0][i] = fa.get(smem, i, 0);
-#pragma unroll
-  for (int j = 0; j < FN; ++j) bfr[0][j] = fb.get(smem + A_BYTES, j, 0);
-
-  for (int t = 0; t < nk; ++t) {
-    // refill the buffer of k-step t-1 (every wave finished reading it
-    // before the barrier that ended k-step t-1)
-    const int tl = t + STAGES - 1;
-    const uint32_t st_l = lds0 + (tl % STAGES) * STAGE;
-    if (tl < nk) {
-      la.issue(st_l, a_k0 + tl * a_step, wid);
-      lb.issue(st_l + A_BYTES, b_k0 + tl * b_step, wid);
-    }
-    const lds_char *As = smem + (t % STAGES) * STAGE;
-#pragma unroll
-    for (int kk = 0; kk < KS; ++kk) {
-      const int c = kk & 1, n = c ^ 1;
-#pragma unroll
-      for (int i = 0; i < FM; ++i)
-#pragma unroll
-        for (int j = 0; j < FN; ++j) acc[i][j] = mfma16(bfr[c][j], af[c][i], acc[i][j]);
-      if constexpr (kDb) {
-        if (do_db) {
-#pragma unroll
-          for (int i = 0; i < FM; ++i) {
-            const u32x4_t w = __builtin_bit_cast(u32x4_t, af[c][i]);
-#pragma unroll
-            for (int e = 0; e < 4; ++e) dbacc[i] = add_pair(w[e], dbacc[i]);
-          }
-        }
-      }
-      if (kk + 1 < KS) {
-#pragma unroll
-        for (int i = 0; i < FM; ++i) af[n][i] = fa.get(As, i, kk + 1);
-#pragma unroll
-        for (int j = 0; j < FN; ++j) bfr[n][j] = fb.get(As + A_BYTES, j, kk + 1);
-        interleave_reads<FM * FN, (FM + FN) * (AT || BT ? 2 : 1)>();
-      } else if (t + 1 < nk) {
-        // also retire this wave's LDS reads of k-step t before the barrier
-        if (t + STAGES - 1 < nk)
-          wait_vmcnt<PER_STAGE * (STAGES - 2), 0>();
-        else
-          wait_vmcnt<0, 0>();
-        asm volatile("" ::: "memory");
-        __builtin_amdgcn_s_barrier();
-        asm volatile("" ::: "memory");
-        const lds_char *Ns = smem + ((t + 1) % STAGES) * STAGE;
-#pragma unroll
-        for (int i = 0; i < FM; ++i) af[n][i] = fa.get(Ns, i, 0);
-#pragma unroll
-        for (int j = 0; j < FN; ++j) bfr[n][j] = fb.get(Ns + A_BYTES, j, 0);
-      }
-    }
-    if constexpr (KS % 2 == 1) {
-      // odd k-steps per stage: the next stage's fragments sit in buffer 1
-#pragma unroll
-      for (int i = 0; i < FM; ++i) af[0][i] = af[1][i];
-#pragma unroll
-      for (int j = 0; j < FN; ++j) bfr[0][j] = bfr[1][j];
-    }
-  }
-  const GemmArgs q = split_outputs(p, split);
-  store_tile_lds<EPI, BM, BN, WM, WN>(q, acc, m0, n0, wm, wn, lane, reinterpret_cast<float *>(smem_raw));
-  if constexpr (kDb) {
-    if (do_db) {
-      // the four 16-lane groups hold the token residues of row lane % 16
-#pragma unroll
-      for (int i = 0; i < FM; ++i) {
-        float tot = dbacc[i] + __shfl_xor(dbacc[i], 16, kWave);
-        tot += __shfl_xor(tot, 32, kWave);
-        const int row = m0 + wm * WTM + i * 16 + (lane & 15);
-        if (lane < 16 && row < q.M) q.db[row] = q.accumulate ? q.db[row] + tot : tot;
-      }
-    }
-  }
-}
-
-template <int BM, int BN, int BK, int WM, int WN, int STAGES, bool AT, bool BT, Epi EPI>
-bool launch_lds_cfg(const GemmArgs &a, uint32_t a_bytes, uint32_t b_bytes, hipStream_t s) {
-  constexpr int NW = WM * WN;
-  constexpr size_t lds = static_cast<size_t>(STAGES) *
-                         (DirectLoader<BM, BK, NW, AT>::BYTES + DirectLoader<BN, BK, NW, BT>::BYTES);
-  static_assert(lds <= 160 * 1024, "LDS budget");
-  const int tiles = ((a.M + BM - 1) / BM) * ((a.N + BN - 1) / BN) * (a.splits > 1 ? a.splits : 1);
-  hipLaunchKernelGGL((gemm_lds_kernel<BM, BN, BK, WM, WN, STAGES, AT, BT, EPI>), dim3(tiles), dim3(WM * WN * 64),
-                     lds, s, a, a_bytes, b_bytes);
-  return true;
-}
-
 template <int BM, int BN, int BK, int WM, int WN, bool AT, bool BT, Epi EPI>
 bool launch_cfg(const GemmArgs &a, hipStream_t s) {
   constexpr int NT = WM * WN * 64;
@@ -1246,6 +981,286 @@ bool launch_half_cfg(const GemmArgs &a, uint32_t a_bytes, uint32_t b_bytes, hipS
   return true;
 }
 
+// ---------------------------------------------------------------------------
+// Ring pipeline for smaller tiles: 8 waves in two groups one slot apart, as
+// above, with one pair of slots per k-step (64 wide): L reads all of the
+// k-step's fragments and issues this wave's share of the k-step S - 1 ahead,
+// M issues its MFMAs.  A small tile's k-step is short, so the loads need
+// several k-steps of lead: S stages fill the LDS.
+//
+// K-step t is read by group 0 in slot 2t and by group 1 in slot 2t + 1, both
+// retired before the barrier that ends the slot; its stage is refilled from
+// slot 2t + 2 on.  Each wave waits for its own share of k-step t + 1 at the
+// end of its L(t), so both groups' shares have landed before slot 2t + 2.
+// ---------------------------------------------------------------------------
+
+// One operand's [ROWS x 64] tile: per-wave loads and fragment addresses.
+template <int ROWS, int F, int S, bool TRANS>
+struct RingTile {
+  static constexpr int BK = 64, KS = 2;
+  static constexpr int LROWS = TRANS ? (ROWS + 63) / 64 * 64 : ROWS;  // (transposed rows padded to 128 bytes)
+  static constexpr int BYTES = LROWS * BK * 2, WB = BYTES / 8, NI = (WB + 1023) / 1024;
+  static constexpr bool MASKED = ROWS != LROWS || WB % 1024 != 0;
+  static constexpr int G = 65536 / BYTES < S ? 65536 / BYTES : S;  // stages one address register reaches
+  static constexpr int NG = (S + G - 1) / G, NOFF = TRANS ? F : KS;
+  static_assert(WB % 16 == 0 && ROWS % 16 == 0 && G >= 1, "tile shape");
+  uint32_t voff[NI];
+  uint64_t mask[NI];
+  u32x4_t rsrc;
+  int off[NG][NOFF];
+
+  // 128-byte multiples alternate between the halves of a 256-byte bank line
+  // from k-row to k-row, so one XOR bit less spreads the eight k-rows
+  __device__ static __forceinline__ int swz(int k) {
+    return LROWS % 128 == 0 ? t_swz(k) : ((((k >> 1) & 1) | (((k >> 3) & 1) << 1)) << 1);
+  }
+  __device__ __forceinline__ void init(const bf16_t *base, uint32_t nbytes, int ld, int r0, int w, int wid, int lane,
+                                       int lds_base) {
+    rsrc = make_rsrc(base, nbytes);
+#pragma unroll
+    for (int i = 0; i < NI; ++i) {
+      const int o = wid * WB + i * 1024 + lane * 16;
+      bool live = i * 1024 + lane * 16 < WB;
+      if constexpr (!TRANS) {
+        using T = NtTile<BK>;
+        const int r = o / T::RB, pch = (o % T::RB) >> 4;
+        const int c = pch ^ ((r / T::RP) % T::CPR);
+        voff[i] = static_cast<uint32_t>(((r0 + r) * static_cast<long>(ld) + c * 8) * 2);
+      } else {
+        const int k = o / (LROWS * 2), pch = (o % (LROWS * 2)) >> 4;
+        const int c = (pch ^ swz(k)) * 8;
+        live = live && c < ROWS;
+        voff[i] = static_cast<uint32_t>((k * static_cast<long>(ld) + r0 + c) * 2);
+      }
+      mask[i] = __ballot(live);
+    }
+#pragma unroll
+    for (int g = 0; g < NG; ++g) {
+      const int gb = lds_base + g * G * BYTES;
+      if constexpr (!TRANS) {
+#pragma unroll
+        for (int kk = 0; kk < KS; ++kk)
+          off[g][kk] = gb + NtTile<BK>::off(w * F * 16 + (lane & 15), kk * 4 + (lane >> 4));
+      } else {
+        const int k = 8 * (lane >> 4) + ((lane & 15) >> 2);
+#pragma unroll
+        for (int f = 0; f < F; ++f) {
+          const int n = w * F * 16 + f * 16 + 4 * (lane & 3);
+          off[g][f] = gb + k * (LROWS * 2) + (((n >> 3) ^ swz(k)) << 4) + (n & 7) * 2;
+        }
+      }
+#pragma unroll
+      for (int i = 0; i < NOFF; ++i) asm volatile("" : "+v"(off[g][i]));
+    }
+  }
+  template <int OFF, int I = 0>
+  __device__ __forceinline__ void issue(uint32_t wbase, uint32_t soff) const {
+    if constexpr (I < NI) {
+      if constexpr (MASKED)
+        issue_lds16<OFF + I * 1024>(rsrc, wbase, voff[I], soff, mask[I]);
+      else
+        issue_lds16<OFF + I * 1024>(rsrc, wbase, voff[I], soff);
+      issue<OFF, I + 1>(wbase, soff);
+    }
+  }
+  template <int ST>
+  __device__ __forceinline__ bf16x8_t get(const lds_char *smem, int f, int kk) const {
+    const lds_char *q = smem + (ST % G) * BYTES;
+    if constexpr (!TRANS) {
+      return *reinterpret_cast<const __attribute__((address_space(3))) bf16x8_t *>(q + off[ST / G][kk] +
+                                                                                     f * 16 * BK * 2);
+    } else {
+      q += off[ST / G][f] + kk * 32 * LROWS * 2;
+      return lds_read_tr(q, q + 4 * LROWS * 2);
+    }
+  }
+};
+
+// f(cnt<0>, cnt<1>, ...).
+template <class F, int... I>
+__device__ __forceinline__ void with_counts(F f, std::integer_sequence<int, I...>) {
+  f(cnt<I>()...);
+}
+
+// Wait until at most r k-steps of PS loads each are in flight.
+template <int PS, int R>
+__device__ __forceinline__ void wait_ksteps(int r) {
+  if constexpr (R > 0) {
+    if (r >= R)
+      wait_vmcnt<R * PS, 0>();
+    else
+      wait_ksteps<PS, R - 1>(r);
+  } else {
+    wait_vmcnt<0, 0>();
+  }
+}
+
+template <int WM, int WN, int FM, int FN, int S, int WGS, bool STAG, bool AT, bool BT, Epi EPI>
+__global__ __launch_bounds__(512, 2 * WGS) void gemm_ring_kernel(GemmArgs p, uint32_t a_bytes, uint32_t b_bytes) {
+  static_assert(WM * WN == 8 && S >= 2, "eight waves, two per SIMD");
+  constexpr int BM = WM * FM * 16, BN = WN * FN * 16, BK = 64, KS = 2, D = S - 1;
+  using TA = RingTile<BM, FM, S, AT>;
+  using TB = RingTile<BN, FN, S, BT>;
+  constexpr int PS = TA::NI + TB::NI, B_BASE = S * TA::BYTES;
+  extern __shared__ __attribute__((aligned(1024))) char smem_raw[];
+  const lds_char *smem = (const lds_char *)(smem_raw);
+
+  const int lane = threadIdx.x & 63;
+  const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int grp = wid >> 2;
+  const int wm = wid / WN, wn = wid % WN;
+  const int tiles_m = (p.M + BM - 1) / BM, tiles_n = (p.N + BN - 1) / BN;
+  int tm, tn, kbeg, klen;
+  const int split = split_of(p, tiles_m, tiles_n, tm, tn, kbeg, klen);
+  const int m0 = tm * BM, n0 = tn * BN;
+
+  TA la;
+  TB lb;
+  const uint32_t lds0 = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(smem));
+  la.init(p.A, a_bytes, p.lda, m0, wm, wid, lane, 0);
+  lb.init(p.B, b_bytes, p.ldb, n0, wn, wid, lane, B_BASE);
+  const uint32_t a_step = AT ? static_cast<uint32_t>(BK) * p.lda * 2 : BK * 2;
+  const uint32_t b_step = BT ? static_cast<uint32_t>(BK) * p.ldb * 2 : BK * 2;
+  uint32_t so_a = AT ? static_cast<uint32_t>(kbeg) * p.lda * 2 : static_cast<uint32_t>(kbeg) * 2;
+  uint32_t so_b = BT ? static_cast<uint32_t>(kbeg) * p.ldb * 2 : static_cast<uint32_t>(kbeg) * 2;
+  const uint32_t wa = __builtin_amdgcn_readfirstlane(lds0 + wid * TA::WB);
+  const uint32_t wb = __builtin_amdgcn_readfirstlane(lds0 + B_BASE + wid * TB::WB);
+
+  f32x4_t acc[FM][FN];
+#pragma unroll
+  for (int i = 0; i < FM; ++i)
+#pragma unroll
+    for (int j = 0; j < FN; ++j) acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+  constexpr bool kDb = (EPI == Epi::kF32) && AT;  // fused bias gradient, as above
+  constexpr int DBF = (FM + WN - 1) / WN;
+  const bool do_db = kDb && p.db != nullptr && tn == 0;
+  float dbacc[DBF];
+#pragma unroll
+  for (int i = 0; i < DBF; ++i) dbacc[i] = 0.f;
+
+  const int nk = (klen + BK - 1) / BK;
+  constexpr std::integral_constant<int, 0> c0{};
+  constexpr std::integral_constant<int, 1> c1{};
+  auto issue = [&](auto st) {
+    la.template issue<st.value * TA::BYTES>(wa, so_a);
+    lb.template issue<st.value * TB::BYTES>(wb, so_b);
+    so_a += a_step;
+    so_b += b_step;
+  };
+  auto barrier = [] {
+    __builtin_amdgcn_sched_barrier(0);
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  bf16x8_t a[KS][FM], b[KS][FN];
+  auto step = [&](auto st, auto full, auto db, int t) {
+    constexpr bool FULL = decltype(full)::value;
+    constexpr int ST = st.value;
+    // ---- L (without stagger: the k-step's only barrier precedes it)
+    if constexpr (!STAG) {
+      if constexpr (FULL)
+        wait_vmcnt<(D - 1) * PS>();
+      else
+        wait_ksteps<PS, D - 1>(min(t + D - 1, nk - 1) - t);
+      barrier();
+    }
+    if (FULL || t + D < nk) issue(cnt<(ST + D) % S>());
+#pragma unroll
+    for (int kk = 0; kk < KS; ++kk) {
+#pragma unroll
+      for (int j = 0; j < FN; ++j) b[kk][j] = lb.template get<ST>(smem, j, kk);
+#pragma unroll
+      for (int i = 0; i < FM; ++i) a[kk][i] = la.template get<ST>(smem, i, kk);
+    }
+    if constexpr (STAG) {
+      if constexpr (FULL)
+        wait_vmcnt<(D - 1) * PS, 0>();
+      else
+        wait_ksteps<PS, D - 1>(min(t + D, nk - 1) - (t + 1));
+      barrier();
+    }
+    // ---- M
+#pragma unroll
+    for (int kk = 0; kk < KS; ++kk)
+#pragma unroll
+      for (int i = 0; i < FM; ++i)
+#pragma unroll
+        for (int j = 0; j < FN; ++j) acc[i][j] = mfma16(b[kk][j], a[kk][i], acc[i][j]);
+    if constexpr (decltype(db)::value) {
+#pragma unroll
+      for (int i = 0; i < FM; ++i) {
+        if (i % WN != wn) continue;
+#pragma unroll
+        for (int kk = 0; kk < KS; ++kk) {
+          const u32x4_t w = __builtin_bit_cast(u32x4_t, a[kk][i]);
+#pragma unroll
+          for (int e = 0; e < 4; ++e) dbacc[i / WN] = add_pair(w[e], dbacc[i / WN]);
+        }
+      }
+    }
+    if constexpr (STAG)
+      barrier();
+    else
+      wait_vmcnt<63, 0>();  // this k-step's reads retired before the next barrier
+  };
+
+  // the first D k-steps
+  with_counts([&](auto... i) { ((i.value < nk ? issue(i) : void()), ...); }, std::make_integer_sequence<int, D>{});
+  if constexpr (STAG) {
+    wait_ksteps<PS, D - 1>(min(D, nk) - 1);
+    barrier();
+    if (grp == 1) barrier();  // group 1 runs one slot behind
+  }
+
+  auto k_loop = [&](auto db) {
+    int t = 0;
+    for (; t + S - 1 + D < nk; t += S)
+      with_counts([&](auto... i) { (step(i, c1, db, t + i.value), ...); }, std::make_integer_sequence<int, S>{});
+    while (t < nk)
+      with_counts([&](auto... i) { ((t < nk ? (step(i, c0, db, t), void(++t)) : void()), ...); },
+                  std::make_integer_sequence<int, S>{});
+  };
+  if constexpr (kDb) {
+    if (do_db)
+      k_loop(c1);
+    else
+      k_loop(c0);
+  } else {
+    k_loop(c0);
+  }
+  if (STAG && grp == 0) barrier();  // match group 1's extra barrier
+
+  const GemmArgs q = split_outputs(p, split);
+  store_tile_lds<EPI, BM, BN, WM, WN>(q, acc, m0, n0, wm, wn, lane, reinterpret_cast<float *>(smem_raw));
+  if constexpr (kDb) {
+    if (do_db) {
+#pragma unroll
+      for (int i = 0; i < DBF; ++i) {
+        float tot = dbacc[i] + __shfl_xor(dbacc[i], 16, kWave);
+        tot += __shfl_xor(tot, 32, kWave);
+        const int f = i * WN + wn;
+        const int row = m0 + (wm * FM + f) * 16 + (lane & 15);
+        if (f < FM && lane < 16 && row < q.M) q.db[row] = q.accumulate ? q.db[row] + tot : tot;
+      }
+    }
+  }
+}
+
+template <int WM, int WN, int FM, int FN, int S, int WGS, bool STAG, bool AT, bool BT, Epi EPI>
+bool launch_ring_cfg(const GemmArgs &a, uint32_t a_bytes, uint32_t b_bytes, hipStream_t s) {
+  constexpr int BM = WM * FM * 16, BN = WN * FN * 16;
+  constexpr size_t pipe = static_cast<size_t>(S) * (RingTile<BM, FM, S, AT>::BYTES + RingTile<BN, FN, S, BT>::BYTES);
+  constexpr size_t epi = static_cast<size_t>(kEpiRows) * (BN + 4) * sizeof(float);
+  constexpr size_t lds = pipe > epi ? pipe : epi;
+  static_assert(lds * WGS <= 160 * 1024, "LDS budget");
+  const int tiles = ((a.M + BM - 1) / BM) * ((a.N + BN - 1) / BN) * (a.splits > 1 ? a.splits : 1);
+  hipLaunchKernelGGL((gemm_ring_kernel<WM, WN, FM, FN, S, WGS, STAG, AT, BT, EPI>), dim3(tiles), dim3(512), lds, s, a,
+                     a_bytes, b_bytes);
+  return true;
+}
+
 // Direct-to-LDS path: pick the tile that minimises (rounds of 256 CUs) x
 // (tile area / per-tile efficiency).  256x256 tiles are the most efficient per
 // tile, 256x192 tiles divide the 6144- and 18432-wide outputs into whole
@@ -1254,19 +1269,30 @@ bool launch_half_cfg(const GemmArgs &a, uint32_t a_bytes, uint32_t b_bytes, hipS
 // Returns false when the operands do not fit the path's constraints.
 template <bool AT, bool BT, Epi EPI>
 bool launch_lds(const GemmArgs &a, hipStream_t s, TileShape t) {
-  constexpr int BK = 64;
   if (!lds_fits(a.M, a.N, a.K, a.lda, a.ldb, AT, BT)) return false;
   // operand extents (bytes) bound the buffer loads
   const uint32_t ab = static_cast<uint32_t>(static_cast<uint64_t>(AT ? a.K : a.M) * a.lda * 2);
   const uint32_t bb = static_cast<uint32_t>(static_cast<uint64_t>(BT ? a.K : a.N) * a.ldb * 2);
+  // Staggered groups pay where a k-step has enough MFMAs to cover the other
+  // group's reads: 128x192 tiles 56.8 against 63.5 us on the ViT-22B shard's
+  // QKV forward; without them 192x128 tiles (two per CU) 31.4 against 39.1 on
+  // the ViT-Base QKV input gradient, 64x128 13.4 against 14.6 at a quarter of
+  // its tokens.  64-row tiles with two strided operands are even or better
+  // with them.
   if (t.bm == 256 && t.bn == 256) return launch_half_cfg<2, 4, 4, 2, AT, BT, EPI>(a, ab, bb, s);
   if (t.bm == 256) return launch_half_cfg<4, 2, 2, 3, AT, BT, EPI>(a, ab, bb, s);
-  return launch_lds_cfg<128, 128, BK, 2, 2, 2, AT, BT, EPI>(a, ab, bb, s);
+  if (t.bm == 128 && t.bn == 256) return launch_ring_cfg<2, 4, 4, 4, 3, 1, true, AT, BT, EPI>(a, ab, bb, s);
+  if (t.bm == 128 && t.bn == 192) return launch_ring_cfg<2, 4, 4, 3, 4, 1, true, AT, BT, EPI>(a, ab, bb, s);
+  if (t.bm == 192) return launch_ring_cfg<4, 2, 3, 4, 2, 2, false, AT, BT, EPI>(a, ab, bb, s);
+  if (t.bm == 128) return launch_ring_cfg<2, 4, 4, 2, 2, 2, false, AT, BT, EPI>(a, ab, bb, s);
+  if (t.bn == 192) return launch_ring_cfg<2, 4, 2, 3, 4, 1, AT, AT, BT, EPI>(a, ab, bb, s);
+  if (t.bn == 128) return launch_ring_cfg<2, 4, 2, 2, 3, 2, AT, AT, BT, EPI>(a, ab, bb, s);
+  return launch_ring_cfg<2, 4, 2, 1, 4, 2, false, AT, BT, EPI>(a, ab, bb, s);
 }
 
 template <bool AT, bool BT, Epi EPI>
 bool launch_lds(const GemmArgs &a, hipStream_t s) {
-  return launch_lds<AT, BT, EPI>(a, s, choose_tile(a.M, a.N, AT && BT));
+  return launch_lds<AT, BT, EPI>(a, s, choose_tile(a.M, a.N, a.K, AT ? kWgrad : BT ? kDgrad : kFwd));
 }
 
 }  // namespace

@@ -53,52 +53,84 @@ inline size_t attn_bwd_ws_bytes(int B, int S, int heads) {
   return static_cast<size_t>(B) * heads * S * sizeof(float);
 }
 
-// ---- GEMM tile shape.  Relative work per unit of time of each tile shape on
-// one CU (256x256 = 1; 0 = never chosen).  256x128 and 128x256 tiles
-// measured 5-15% slower per GEMM than the shapes below on the ViT-22B
-// tensor-parallel shard, where they would fill more CUs, so they stay off.
-// 128x128 tiles (two workgroups per CU) count 0.9 in the forward and
-// input-gradient layouts: at 0.9 the ViT-Base MLP-up forward and MLP-down
-// input gradient take them and ran 11% faster (58 -> 52 and 61 -> 53 us),
-// while no other product of the five workloads changed tile.  The weight
-// gradients keep 0.75: at 0.9 the ViT-22B shard's MLP weight gradients would
-// take them, and one of the two ran 3% slower.
-constexpr double kEff256x256 = 1.0, kEff256x192 = 0.95, kEff256x128 = 0.0, kEff128x256 = 0.0;
-constexpr double kEff128x128 = 0.9, kEff128x128Wgrad = 0.75;
+// ---- GEMM tile choice.  The direct-to-LDS kernels come in these output
+// tiles; per_cu workgroups of a tile share a CU.  cost[layout] is the time in
+// us of one workgroup per 64-wide k-step and on top of them (prologue,
+// epilogue, launch), {step, rest}, alone on its CU and, where two share a CU,
+// of such a pair.  Fitted to 28 products per layout (ViT-Tiny to ViT-10B and
+// the ViT-22B shard: outputs 192 to 16384 wide, contractions 192 to 16384,
+// every tile timed on each): the fit is within 3-12% of the measured times
+// on average, and the tiles it picks took 1.5% longer in total than the best
+// tile of each product, 18% less than the rule this replaces (256x256, 256x192
+// or 128x128 tiles by area and rounds).  Small tiles pay more per flop (each
+// loads (bm + bn) / (bm * bn) operand bytes per flop into LDS, and a short
+// k-step is bound by its barrier and LDS latency) but fill the 256 CUs.
+enum GemmLayout { kFwd = 0, kDgrad = 1, kWgrad = 2 };
 
 struct TileShape {
   int bm, bn;
 };
 
-// The tile that minimises (rounds of 256 CUs) x (tile area / efficiency);
-// wgrad selects the weight-gradient layout's efficiencies.
-inline TileShape choose_tile(int M, int N, bool wgrad) {
-  auto cost = [&](int bm, int bn, double eff) {
-    if (eff <= 0.0) return 1e300;
-    const long tiles = static_cast<long>((M + bm - 1) / bm) * ((N + bn - 1) / bn);
-    return static_cast<double>((tiles + 255) / 256) * bm * bn / eff;
-  };
-  const TileShape shapes[5] = {{256, 256}, {256, 192}, {256, 128}, {128, 256}, {128, 128}};
-  const double eff[5] = {kEff256x256, kEff256x192, kEff256x128, kEff128x256, wgrad ? kEff128x128Wgrad : kEff128x128};
-  int best = 0;
-  for (int i = 1; i < 5; ++i)
-    if (cost(shapes[i].bm, shapes[i].bn, eff[i]) < cost(shapes[best].bm, shapes[best].bn, eff[best])) best = i;
-  return shapes[best];
+struct TileCost {
+  int bm, bn, per_cu;
+  float cost[3][4];  // [layout]: step, rest, step of a pair, rest of a pair
+};
+
+constexpr TileCost kTiles[] = {
+    {256, 256, 1, {{0.95, 11.15, 0.00, 0.00}, {0.91, 10.89, 0.00, 0.00}, {1.24, 9.25, 0.00, 0.00}}},
+    {256, 192, 1, {{0.78, 10.58, 0.00, 0.00}, {0.81, 9.58, 0.00, 0.00}, {1.02, 8.98, 0.00, 0.00}}},
+    {128, 256, 1, {{0.60, 7.46, 0.00, 0.00}, {0.59, 8.86, 0.00, 0.00}, {0.61, 8.57, 0.00, 0.00}}},
+    {128, 192, 1, {{0.53, 6.53, 0.00, 0.00}, {0.52, 7.02, 0.00, 0.00}, {0.56, 5.71, 0.00, 0.00}}},
+    {192, 128, 2, {{0.70, 5.50, 1.08, 8.47}, {0.70, 5.50, 1.02, 12.49}, {0.75, 4.32, 1.13, 7.78}}},
+    {128, 128, 2, {{0.60, 3.53, 0.73, 6.58}, {0.56, 4.58, 0.70, 8.23}, {0.66, 0.77, 0.88, 4.44}}},
+    {64, 192, 1, {{0.40, 3.57, 0.00, 0.00}, {0.37, 4.06, 0.00, 0.00}, {0.40, 3.47, 0.00, 0.00}}},
+    {64, 128, 2, {{0.28, 2.68, 0.55, 2.43}, {0.28, 2.08, 0.52, 3.58}, {0.30, 2.66, 0.55, 2.21}}},
+    {64, 64, 2, {{0.17, 3.17, 0.35, 1.34}, {0.19, 1.65, 0.37, 1.07}, {0.25, 0.24, 0.39, 0.42}}}};
+
+// Predicted time (us) of `wgs` workgroups of a tile with nk k-steps each, in
+// rounds of per_cu workgroups on every CU.
+inline float gemm_cost(const TileCost &t, GemmLayout l, long wgs, int nk) {
+  const float *c = t.cost[l];
+  if (t.per_cu == 1) return static_cast<float>((wgs + 255) / 256) * (nk * c[0] + c[1]);
+  const long full = wgs / 512, rem = wgs - full * 512;
+  const float one = nk * c[0] + c[1], two = nk * c[2] + c[3];
+  return static_cast<float>(full) * two + (rem == 0 ? 0.f : rem > 256 ? two : one);
 }
 
-// ---- Split of the contraction.  A product whose output is a small grid of
-// 256 x 256 tiles is split over its contraction (the tokens, for a weight
-// gradient): each split writes fp32 partials and a second kernel adds them
-// in split order (deterministic).  Splits run 128 x 128 tiles, as many splits
-// as fill two workgroups on each of the 256 CUs, each covering at least
-// kMinSplitTokens of the contraction in a whole number of 64-wide k-steps
-// (the last split takes the remainder).  Same-box A/B of the split kernels
-// alone (us): with 256 x 256 tiles split to fill the CUs once, the ViT-Base
-// weight gradients took 60, 58, 35 and 47 (MLP-down, MLP-up, out-projection,
-// QKV); with the 128 x 128 splits 53, 56, 26 and 40, the ViT-Huge
-// out-projection weight gradient 39 -> 30 and the ViT-22B shard's
-// out-projection input gradient 44 -> 36.  In the layer chain ViT-Base went
-// from 0.665 to 0.631 ms per step; ViT-Huge and the shard were unchanged.
+inline long tile_count(const TileCost &t, int M, int N) {
+  return static_cast<long>((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn);
+}
+
+struct TilePick {
+  TileShape tile;
+  float us;
+};
+
+inline TilePick pick_tile(int M, int N, int K, GemmLayout l) {
+  TilePick best{{0, 0}, 0.f};
+  for (const TileCost &t : kTiles) {
+    // weight gradients over a few k-steps are their fp32 stores: 64-row tiles
+    // (whose loop is cheap, not their epilogue) only beyond five of them
+    if (l == kWgrad && t.bm < 128 && K <= 5 * 64) continue;
+    const float us = gemm_cost(t, l, tile_count(t, M, N), (K + 63) / 64);
+    if (best.tile.bm == 0 || us < best.us) best = {{t.bm, t.bn}, us};
+  }
+  return best;
+}
+
+inline TileShape choose_tile(int M, int N, int K, GemmLayout l) { return pick_tile(M, N, K, l).tile; }
+
+// ---- Split of the contraction (the tokens, for a weight gradient), for
+// products whose output is small: each split writes fp32 partials and a second
+// kernel adds them in split order (deterministic).  Weight gradients of at
+// most 64 tiles of 256x256, and forward and input-gradient products of at most
+// 32, split when their contraction holds two splits of kMinSplitTokens; which
+// products split is part of what callers size their workspaces by.  Tile and
+// number of splits minimise the cost model's time plus the second kernel's (5
+// us and its traffic at 4.5 TB/s, as measured on outputs of 0.3 to 2.4 M
+// values); every split covers at least kMinSplitTokens in whole 64-wide
+// k-steps (the last takes the remainder).  Tiles below 128x128 are worth it
+// only for forward and input-gradient products, where they fill the CUs.
 constexpr int kMinSplitTokens = 512, kMaxSplits = 16;
 
 struct SplitPlan {
@@ -106,45 +138,49 @@ struct SplitPlan {
   TileShape tile;
 };
 
-inline SplitPlan split_128(int M, int N, int K) {
-  const long tiles = static_cast<long>((M + 127) / 128) * ((N + 127) / 128);
-  int S = static_cast<int>(std::min<long>(512 / tiles, std::min(K / kMinSplitTokens, kMaxSplits)));
-  if (S > 1) {
-    const int kc = ((K + S - 1) / S + 63) / 64 * 64;
-    S = (K + kc - 1) / kc;
-    if (S > 1) return {S, kc, {128, 128}};
+inline SplitPlan best_split(int M, int N, int K, GemmLayout l) {
+  SplitPlan best{1, K, {0, 0}};
+  float best_us = 0.f;
+  const int max_s = std::min(K / kMinSplitTokens, kMaxSplits);
+  for (const TileCost &t : kTiles) {
+    const bool small = t.bm * t.bn < 128 * 128;
+    if (l == kWgrad ? t.bm < 128 : !small && (t.bm != 128 || t.bn != 128)) continue;
+    const long n = tile_count(t, M, N);
+    for (int s = 2; s <= max_s && (s == 2 || n * s <= 1024); ++s) {
+      if (l != kWgrad && small && n * s <= 256) continue;
+      const int kc = ((K + s - 1) / s + 63) / 64 * 64;
+      if ((K + kc - 1) / kc != s) continue;
+      const float us = gemm_cost(t, l, n * s, kc / 64) +
+                       static_cast<float>(s + 1) * static_cast<float>(M) * static_cast<float>(N) * (4.f / 4.5e6f);
+      if (best.splits == 1 || us < best_us) {
+        best_us = us;
+        best = {s, kc, {t.bm, t.bn}};
+      }
+    }
   }
-  return {1, K, {0, 0}};
+  return best;
 }
 
-// Weight gradient (M output rows, N output columns, K tokens): split when
-// the output has at most 64 tiles of 256 x 256 (a quarter of the CUs).
-// Measured per layer with the earlier 256 x 256 splits (ViT-Base / ViT-Huge /
-// ViT-22B shard, four weight gradients): 351 -> 201 us, 287 -> 268 us,
-// 299 -> 299 us against no split; splitting outputs of up to 128 tiles lost
-// 10-20 us on the ViT-Huge MLP and shard out-projection gradients.
+inline long tiles_256(int M, int N) { return static_cast<long>((M + 255) / 256) * ((N + 255) / 256); }
+
+// Weight gradient: M output rows, N output columns, K tokens.
 inline SplitPlan wgrad_split_plan(int M, int N, int K) {
-  const long tiles = static_cast<long>((M + 255) / 256) * ((N + 255) / 256);
-  if (tiles * 4 <= 256) {
-    const SplitPlan sp = split_128(M, N, K);
+  if (K >= 2 * kMinSplitTokens && tiles_256(M, N) <= 64) {
+    const SplitPlan sp = best_split(M, N, K, kWgrad);
     if (sp.splits > 1) return sp;
   }
-  return {1, K, choose_tile(M, N, true)};
+  return {1, K, choose_tile(M, N, K, kWgrad)};
 }
 
 // Forward / input-gradient product (output [M, N], contraction K over
-// k-contiguous rows, so K a multiple of 64): split when the output has at
-// most 32 tiles of 256 x 256 (an eighth of the CUs).  The partials' round
-// trip and the separate epilogue pay off only for such very small grids:
-// with up to 128 tiles the ViT-Base and ViT-Huge forward and input-gradient
-// products with 75-96 tiles ran 5-14 us slower split.
+// k-contiguous rows, so K a multiple of 64).  One plan for both: their
+// workspace query does not tell them apart.
 inline SplitPlan gemm_split_plan(int M, int N, int K) {
-  const long tiles = static_cast<long>((M + 255) / 256) * ((N + 255) / 256);
-  if (K % 64 == 0 && tiles * 8 <= 256) {
-    const SplitPlan sp = split_128(M, N, K);
+  if (K % 64 == 0 && K >= 2 * kMinSplitTokens && tiles_256(M, N) <= 32) {
+    const SplitPlan sp = best_split(M, N, K, kFwd);
     if (sp.splits > 1) return sp;
   }
-  return {1, K, choose_tile(M, N, false)};
+  return {1, K, choose_tile(M, N, K, kFwd)};
 }
 
 // Whether the direct-to-LDS kernels take a product (operands A(m, k) and
@@ -182,7 +218,7 @@ inline GemmPlan gemm_plan(int M, int N, int K, int lda, int ldb, bool AT, bool B
   const SplitPlan sp = wgrad ? wgrad_split_plan(M, N, K) : gemm_split_plan(M, N, K);
   const bool split_ok = wgrad ? M % 4 == 0 && N % 4 == 0 : N % 8 == 0;
   if (sp.splits > 1 && split_ok && fits) return {sp.tile, sp.splits};
-  if (fits) return {choose_tile(M, N, wgrad), 1};
+  if (fits) return {choose_tile(M, N, K, wgrad ? kWgrad : BT ? kDgrad : kFwd), 1};
   return {any_tile(M, N), 1};
 }
 
