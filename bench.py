@@ -101,18 +101,19 @@ def gemm_products(cfg):
             "qkv_bwd_weight": ("wgrad", M, 3 * A, H)}
 
 
-def _tile_of(pid, nb, tiles_m, tiles_n):
+def _tile_of(pid, nb, tiles_m, tiles_n, gm=4):
     """Output tile of workgroup pid in an unsplit GEMM grid of nb workgroups,
-    in the kernels' order (workgroup i runs on XCD i % 8): with an even grid,
-    two M-halves of four XCDs each, every XCD walking its block in groups of
-    4 row tiles; otherwise one contiguous range of tiles per XCD, in groups
-    of 8 row tiles."""
+    in the kernels' order (workgroup i runs on XCD i % 8): with an even grid
+    of at least 2 * gm row tiles, two M-halves of four XCDs each, every XCD
+    walking its block in groups of gm row tiles (4 for 256-row tiles, else 8);
+    otherwise one contiguous range of tiles per XCD, in groups of 8 row
+    tiles."""
     xcd, local = pid & 7, pid >> 3
-    if tiles_m % 2 == 0 and tiles_n % 4 == 0:
+    if tiles_m % 2 == 0 and tiles_n % 4 == 0 and tiles_m >= 2 * gm:
         rows_p, cols_x = tiles_m // 2, tiles_n // 4
-        g, in_g = divmod(local, 4 * cols_x)
-        gm = min(rows_p - 4 * g, 4)
-        return (xcd >> 2) * rows_p + 4 * g + in_g % gm, (xcd & 3) * cols_x + in_g // gm
+        g, in_g = divmod(local, gm * cols_x)
+        rows = min(rows_p - gm * g, gm)
+        return (xcd >> 2) * rows_p + gm * g + in_g % rows, (xcd & 3) * cols_x + in_g // rows
     per, rem = nb >> 3, nb & 7
     logical = xcd * (per + 1) + local if xcd < rem else rem * (per + 1) + (xcd - rem) * per + local
     g, in_g = divmod(logical, 8 * tiles_n)
@@ -147,7 +148,7 @@ def fetch_floor(rows, cols, K, bm, bn, splits):
     for r0 in range(0, nb, per_round):
         panels = {}
         for pid in range(r0, min(nb, r0 + per_round)):
-            sp, a, b = _split_item(pid, nb, tm, tn) if splits > 1 else (0, *_tile_of(pid, nb, tm, tn))
+            sp, a, b = _split_item(pid, nb, tm, tn) if splits > 1 else (0, *_tile_of(pid, nb, tm, tn, 4 if bm == 256 else 8))
             klen = min(K - sp * kc, kc)
             rs, cs = panels.setdefault(pid & 7, (set(), set()))
             rs.add((a, sp, min(bm, rows - a * bm) * klen))

@@ -558,7 +558,9 @@ int enc_calib_copy(const void *src, void *dst, size_t bytes, enc_stream_t stream
  * traffic or dispatches: the output tile (*tile_rows x *tile_cols of the
  * output as stored) and the number of contraction splits (*splits, 1 when
  * not split) that the entry points use when given a workspace of the size
- * their query returns (with ws = NULL nothing is split).  layout:
+ * their query returns (with ws = NULL nothing is split).  The products with a
+ * GELU or GELU' epilogue (enc_mlp_up_fwd, enc_mlp_down_bwd_data) may run
+ * another tile, as their epilogue is longer; their splits are the same.  layout:
  *   ENC_LAYOUT_FWD    the forward projections: output [M, N] = X[M, K] W^T
  *   ENC_LAYOUT_DGRAD  the input gradients: output [M, N] = dY[M, K] W[K, N]
  *   ENC_LAYOUT_WGRAD  the weight gradients: dW[N, K] over M tokens (M, N, K

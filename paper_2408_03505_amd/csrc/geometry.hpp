@@ -54,18 +54,22 @@ inline size_t attn_bwd_ws_bytes(int B, int S, int heads) {
 }
 
 // ---- GEMM tile choice.  The direct-to-LDS kernels come in these output
-// tiles; per_cu workgroups of a tile share a CU.  cost[layout] is the time in
-// us of one workgroup per 64-wide k-step and on top of them (prologue,
-// epilogue, launch), {step, rest}, alone on its CU and, where two share a CU,
-// of such a pair.  Fitted to 28 products per layout (ViT-Tiny to ViT-10B and
-// the ViT-22B shard: outputs 192 to 16384 wide, contractions 192 to 16384,
-// every tile timed on each): the fit is within 3-12% of the measured times
-// on average, and the tiles it picks took 1.5% longer in total than the best
-// tile of each product, 18% less than the rule this replaces (256x256, 256x192
-// or 128x128 tiles by area and rounds).  Small tiles pay more per flop (each
+// tiles; per_cu workgroups of a tile share a CU.  cost[kind] is the time in us
+// of one workgroup per 64-wide k-step and on top of them (prologue, epilogue):
+// {step, rest} alone on its CU and, where two share a CU, {step, rest} of such
+// a pair.  Fitted to 28 products per layout (ViT-Tiny to ViT-10B and the
+// ViT-22B shard: outputs 192 to 16384 wide, contractions 192 to 16384, every
+// tile timed on each): the fit is within 3-8% of the measured times on
+// average, and the tiles it picks took 1.5% longer in total than the best tile
+// of each product, 18% less than the rule this replaces (256x256, 256x192 or
+// 128x128 tiles by area and rounds).  Small tiles pay more per flop (each
 // loads (bm + bn) / (bm * bn) operand bytes per flop into LDS, and a short
 // k-step is bound by its barrier and LDS latency) but fill the 256 CUs.
-enum GemmLayout { kFwd = 0, kDgrad = 1, kWgrad = 2 };
+// Products with a GELU or GELU' epilogue have rows of their own: the epilogue
+// of a 256x256 tile takes 21 and 24 us there against 10 and 7, and tiles two
+// to a CU hide it behind each other's loops (ViT-Base MLP-up forward 46 us on
+// 128x128 tiles against 59 on 256x192).
+enum GemmLayout { kFwd = 0, kDgrad = 1, kWgrad = 2, kFwdGelu = 3, kDgradGelu = 4 };
 
 struct TileShape {
   int bm, bn;
@@ -73,19 +77,19 @@ struct TileShape {
 
 struct TileCost {
   int bm, bn, per_cu;
-  float cost[3][4];  // [layout]: step, rest, step of a pair, rest of a pair
+  float cost[5][4];  // [GemmLayout]: step, rest, step of a pair, rest of a pair
 };
 
 constexpr TileCost kTiles[] = {
-    {256, 256, 1, {{0.95, 11.15, 0.00, 0.00}, {0.91, 10.89, 0.00, 0.00}, {1.24, 9.25, 0.00, 0.00}}},
-    {256, 192, 1, {{0.78, 10.58, 0.00, 0.00}, {0.81, 9.58, 0.00, 0.00}, {1.02, 8.98, 0.00, 0.00}}},
-    {128, 256, 1, {{0.60, 7.46, 0.00, 0.00}, {0.59, 8.86, 0.00, 0.00}, {0.61, 8.57, 0.00, 0.00}}},
-    {128, 192, 1, {{0.53, 6.53, 0.00, 0.00}, {0.52, 7.02, 0.00, 0.00}, {0.56, 5.71, 0.00, 0.00}}},
-    {192, 128, 2, {{0.70, 5.50, 1.08, 8.47}, {0.70, 5.50, 1.02, 12.49}, {0.75, 4.32, 1.13, 7.78}}},
-    {128, 128, 2, {{0.60, 3.53, 0.73, 6.58}, {0.56, 4.58, 0.70, 8.23}, {0.66, 0.77, 0.88, 4.44}}},
-    {64, 192, 1, {{0.40, 3.57, 0.00, 0.00}, {0.37, 4.06, 0.00, 0.00}, {0.40, 3.47, 0.00, 0.00}}},
-    {64, 128, 2, {{0.28, 2.68, 0.55, 2.43}, {0.28, 2.08, 0.52, 3.58}, {0.30, 2.66, 0.55, 2.21}}},
-    {64, 64, 2, {{0.17, 3.17, 0.35, 1.34}, {0.19, 1.65, 0.37, 1.07}, {0.25, 0.24, 0.39, 0.42}}}};
+    {256, 256, 1, {{0.94, 9.75}, {0.93, 7.29}, {1.24, 9.25}, {0.94, 20.98}, {0.93, 24.05}}},
+    {256, 192, 1, {{0.78, 9.38}, {0.83, 6.73}, {1.02, 8.98}, {0.78, 18.60}, {0.83, 19.00}}},
+    {128, 256, 1, {{0.60, 6.15}, {0.64, 4.66}, {0.61, 8.57}, {0.60, 12.24}, {0.64, 13.03}}},
+    {128, 192, 1, {{0.53, 5.89}, {0.55, 4.33}, {0.56, 5.71}, {0.53, 9.03}, {0.55, 9.02}}},
+    {192, 128, 2, {{0.72, 5.00, 0.97, 7.44}, {0.74, 4.50, 1.07, 2.36}, {0.75, 4.32, 1.13, 7.78}, {0.72, 9.50, 0.97, 20.00}, {0.74, 8.06, 1.07, 12.80}}},
+    {128, 128, 2, {{0.54, 7.89, 0.73, 5.68}, {0.59, 2.84, 0.74, 4.58}, {0.66, 0.77, 0.88, 4.44}, {0.54, 5.38, 0.73, 9.17}, {0.59, 4.71, 0.74, 9.63}}},
+    {64, 192, 1, {{0.39, 3.37}, {0.38, 2.90}, {0.40, 3.47}, {0.39, 5.62}, {0.38, 6.43}}},
+    {64, 128, 2, {{0.29, 2.50, 0.54, 2.18}, {0.28, 1.92, 0.53, 1.72}, {0.30, 2.66, 0.55, 2.21}, {0.29, 5.90, 0.54, 3.62}, {0.28, 7.95, 0.53, 3.77}}},
+    {64, 64, 2, {{0.17, 3.20, 0.36, 0.94}, {0.20, 0.86, 0.37, 0.77}, {0.25, 0.24, 0.39, 0.42}, {0.12, 2.94, 0.36, 1.46}, {0.20, 2.00, 0.37, 2.40}}}};
 
 // Predicted time (us) of `wgs` workgroups of a tile with nk k-steps each, in
 // rounds of per_cu workgroups on every CU.
