@@ -23,6 +23,7 @@
 #include <algorithm>
 #include <atomic>
 #include <mutex>
+#include <type_traits>
 
 #include "common.hpp"
 #include "kernels.hpp"
@@ -197,52 +198,57 @@ __device__ __forceinline__ void tile_issue(const u32x4_t &rsrc, uint32_t lds_til
   }
 }
 
-// Wait for the oldest tile in flight: with `ahead` later tiles already issued
-// (each L loads per wave) those may stay outstanding.
-template <int L>
-__device__ __forceinline__ void wait_tiles(int ahead) {
-  if (ahead >= 2)
-    wait_vmcnt<2 * L>();
-  else if (ahead == 1)
-    wait_vmcnt<L>();
-  else
-    wait_vmcnt<0>();
-}
-
 __device__ __forceinline__ void block_barrier() {
   asm volatile("" ::: "memory");
   __builtin_amdgcn_s_barrier();
   asm volatile("" ::: "memory");
 }
 
-// MFMA A operand (rows = tile rows rbase.., contraction = columns 16kk..) by ds_read_b128.
-__device__ __forceinline__ bf16x8_t tile_rows(const lds_char *t, int rbase, int kk, int lane) {
-  return *reinterpret_cast<const __attribute__((address_space(3))) bf16x8_t *>(
-      t + tile_off(rbase + (lane & 31), kk * 2 + (lane >> 5)));
-}
-
-// MFMA A operand (rows = columns nbase.., contraction = tile rows 16st..) by
-// two ds_read_b64_tr_b16.
-__device__ __forceinline__ bf16x8_t tile_cols(const lds_char *t, int nbase, int st, int lane) {
-  const int k = st * 16 + 8 * (lane >> 5) + ((lane & 15) >> 2);
-  const int n = nbase + 16 * ((lane >> 4) & 1) + 4 * (lane & 3);
-  const int in = (n & 7) * 2;
-  return lds_read_tr(t + tile_off(k, n >> 3) + in, t + tile_off(k + 4, n >> 3) + in);
-}
-
-// As tile_cols, but contraction index kk reads tile row 16st + perm23(kk):
-// the operand then meets registers whose tokens come in the order a
-// 32x32 MFMA result leaves them (bits 2 and 3 of the token index swapped),
-// so one natural-order tile serves both the row reads and this read.  The
-// transpose read takes each source lane's row address; lane half h (lanes
-// 32h..) supplies rows 4h + (lane % 16) / 4 for elements 0..3 and those
-// rows + 8 for elements 4..7.
-__device__ __forceinline__ bf16x8_t tile_cols_perm(const lds_char *t, int nbase, int st, int lane) {
-  const int k = st * 16 + 4 * (lane >> 5) + ((lane & 15) >> 2);
-  const int n = nbase + 16 * ((lane >> 4) & 1) + 4 * (lane & 3);
-  const int in = (n & 7) * 2;
-  return lds_read_tr(t + tile_off(k, n >> 3) + in, t + tile_off(k + 8, n >> 3) + in);
-}
+// This lane's LDS addresses of the two read patterns of a tile, relative to
+// the tile.  They stay in registers, and the loops are unrolled over the two
+// tile stages so that stage, fragment and step go in the reads' offset field:
+// computed per read, the addresses were a sixth of the loops' vector work,
+// which the matrix instructions of the SIMD's other waves compete with.
+//
+// row(f, kk): MFMA A operand (rows = tile rows 32f.., contraction = columns
+// 16kk..) by ds_read_b128.
+// col(nf, st): MFMA A operand (rows = columns 32nf.., contraction = tile rows
+// 16st..) by two ds_read_b64_tr_b16.  With PERM, contraction index kk reads
+// tile row 16st + perm23(kk): the operand then meets registers whose tokens
+// come in the order a 32x32 MFMA result leaves them (bits 2 and 3 of the token
+// index swapped), so one natural-order tile serves both the row reads and
+// this read.  The transpose read takes each source lane's row address; lane
+// half h (lanes 32h..) supplies rows 4h + (lane % 16) / 4 for elements 0..3
+// and those rows + 8 for elements 4..7.
+template <int D, bool PERM>
+struct TileReads {
+  using H = Head<D>;
+  int row_off[H::KS], col_off[H::NF][2];
+  // row_base, col_base: LDS offsets of the tiles the two patterns read, in stage 0
+  __device__ __forceinline__ void init(int lane, int row_base, int col_base) {
+#pragma unroll
+    for (int kk = 0; kk < H::KS; ++kk) {
+      row_off[kk] = row_base + tile_off(lane & 31, kk * 2 + (lane >> 5));
+      asm volatile("" : "+v"(row_off[kk]));
+    }
+    const int k = (PERM ? 4 : 8) * (lane >> 5) + ((lane & 15) >> 2);
+#pragma unroll
+    for (int nf = 0; nf < H::NF; ++nf) {
+      const int n = nf * 32 + 16 * ((lane >> 4) & 1) + 4 * (lane & 3);
+      col_off[nf][0] = col_base + tile_off(k, n >> 3) + (n & 7) * 2;
+      col_off[nf][1] = col_base + tile_off(k + (PERM ? 8 : 4), n >> 3) + (n & 7) * 2;
+      asm volatile("" : "+v"(col_off[nf][0]), "+v"(col_off[nf][1]));
+    }
+  }
+  // stage: LDS address of the stage's offset 0
+  __device__ __forceinline__ bf16x8_t row(const lds_char *stage, int f, int kk) const {
+    return *reinterpret_cast<const __attribute__((address_space(3))) bf16x8_t *>(stage + f * 32 * kDL * 2 + row_off[kk]);
+  }
+  __device__ __forceinline__ bf16x8_t col(const lds_char *stage, int nf, int st) const {
+    const lds_char *q = stage + st * 16 * kDL * 2;
+    return lds_read_tr(q + col_off[nf][0], q + col_off[nf][1]);
+  }
+};
 
 // A operands of a token-contracting product (columns nf*32.. of a tile,
 // contraction over its rows), read ahead of the work they wait on when the
@@ -250,31 +256,32 @@ __device__ __forceinline__ bf16x8_t tile_cols_perm(const lds_char *t, int nbase,
 template <int D, int KT, bool PRE, bool PERM>
 struct ColOperands {
   bf16x8_t v[PRE ? KT / 16 : 1][PRE ? Head<D>::NF : 1];
-  __device__ __forceinline__ void fetch(const lds_char *t, int lane) {
+  __device__ __forceinline__ void fetch(const lds_char *stage, const TileReads<D, PERM> &r) {
     if constexpr (PRE) {
 #pragma unroll
       for (int st = 0; st < KT / 16; ++st)
 #pragma unroll
-        for (int nf = 0; nf < Head<D>::NF; ++nf)
-          v[st][nf] = PERM ? tile_cols_perm(t, nf * 32, st, lane) : tile_cols(t, nf * 32, st, lane);
+        for (int nf = 0; nf < Head<D>::NF; ++nf) v[st][nf] = r.col(stage, nf, st);
     }
   }
-  __device__ __forceinline__ bf16x8_t get(const lds_char *t, int nf, int st, int lane) const {
+  __device__ __forceinline__ bf16x8_t get(const lds_char *stage, const TileReads<D, PERM> &r, int nf, int st) const {
     if constexpr (PRE)
       return v[st][nf];
     else
-      return PERM ? tile_cols_perm(t, nf * 32, st, lane) : tile_cols(t, nf * 32, st, lane);
+      return r.col(stage, nf, st);
   }
 };
 
-template <int D, int KT, int ST, int MINB>
+template <int N>
+using Stage = std::integral_constant<int, N>;
+
+template <int D, int KT, int MINB>
 __global__ __launch_bounds__(256, MINB) void attn_fwd_kernel(int B, int S, int heads, const bf16_t *__restrict__ qkv,
                                                           uint32_t qkv_bytes, bf16_t *__restrict__ o,
                                                           float *__restrict__ lse) {
   using H = Head<D>;
   constexpr int TB = tile_bytes<KT>(), NL = TileLoads<KT, 4>::N;
-  static_assert(ST == 2 || ST == 3, "two or three tile stages");
-  extern __shared__ __attribute__((aligned(1024))) char smem_raw[];  // ST x (K tile, V tile)
+  extern __shared__ __attribute__((aligned(1024))) char smem_raw[];  // 2 x (K tile, V tile)
   const lds_char *smem = (const lds_char *)(smem_raw);
   const uint32_t lds0 = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(smem));
 
@@ -298,7 +305,7 @@ __global__ __launch_bounds__(256, MINB) void attn_fwd_kernel(int B, int S, int h
   const uint32_t v_base = k_base + static_cast<uint32_t>(A * 2);
   const uint32_t tile_step = static_cast<uint32_t>(KT * ld * 2);
   auto issue = [&](int t) {
-    const uint32_t buf = lds0 + (t % ST) * 2 * TB;
+    const uint32_t buf = lds0 + (t & 1) * 2 * TB;
     const int rem = S - t * KT;
     tile_issue<KT, 4>(rsrc, buf, voff_k, k_base + t * tile_step, wid, lane, rem, ld, false);
     tile_issue<KT, 4>(rsrc, buf + TB, voff_v, v_base + t * tile_step, wid, lane, rem, ld, true);
@@ -313,17 +320,17 @@ __global__ __launch_bounds__(256, MINB) void attn_fwd_kernel(int B, int S, int h
   float m = -INFINITY, l = 0.f;
   const float c = kLog2e / sqrtf(static_cast<float>(D));
 
+  TileReads<D, false> rd;
+  rd.init(lane, 0, TB);
   const int nk = (S + KT - 1) / KT;
-  for (int t = 0; t < ST - 1 && t < nk; ++t) issue(t);
-  for (int t = 0; t < nk; ++t) {
-    // this wave's loads of tile t have landed (those of later tiles may stay in flight)
-    wait_tiles<2 * NL>(min(nk - 1 - t, ST - 2));
+  issue(0);
+  auto tile = [&](auto stage, int t) {
+    wait_vmcnt<0>();  // this wave's loads of tile t have landed
     // every wave's loads of tile t have landed, and every wave is done with
     // tile t - 1, whose buffer the next issue refills
     block_barrier();
-    if (t + ST - 1 < nk) issue(t + ST - 1);
-    const lds_char *Ks = smem + (t % ST) * 2 * TB;
-    const lds_char *Vs = Ks + TB;
+    if (t + 1 < nk) issue(t + 1);
+    const lds_char *Ts = smem + stage.value * 2 * TB;
     const int k0 = t * KT;
     if (active) {  // waves whose queries all lie past the sequence only load and synchronise
     constexpr int NS = KT / 32;  // 32-key fragments per tile
@@ -332,10 +339,10 @@ __global__ __launch_bounds__(256, MINB) void attn_fwd_kernel(int B, int S, int h
     for (int f = 0; f < NS; ++f) {
       s[f] = f32x16_t{};
 #pragma unroll
-      for (int kk = 0; kk < H::KS; ++kk) s[f] = mfma32(tile_rows(Ks, f * 32, kk, lane), qf[kk], s[f]);
+      for (int kk = 0; kk < H::KS; ++kk) s[f] = mfma32(rd.row(Ts, f, kk), qf[kk], s[f]);
     }
     ColOperands<D, KT, (D <= kPrefetchMaxD), false> vop;  // V^T operands, read under the softmax
-    vop.fetch(Vs, lane);
+    vop.fetch(Ts, rd);
     if (k0 + KT > S) {  // the sequence's last, partial tile: keys past it get no weight
 #pragma unroll
       for (int f = 0; f < NS; ++f)
@@ -379,9 +386,13 @@ __global__ __launch_bounds__(256, MINB) void attn_fwd_kernel(int B, int S, int h
     for (int st = 0; st < KT / 16; ++st) {
       const bf16x8_t pb = pack8(s[st >> 1], st & 1);
 #pragma unroll
-      for (int nf = 0; nf < H::NF; ++nf) acc[nf] = mfma32(vop.get(Vs, nf, st, lane), pb, acc[nf]);
+      for (int nf = 0; nf < H::NF; ++nf) acc[nf] = mfma32(vop.get(Ts, rd, nf, st), pb, acc[nf]);
     }
     }
+  };
+  for (int t = 0; t < nk; t += 2) {
+    tile(Stage<0>(), t);
+    if (t + 1 < nk) tile(Stage<1>(), t + 1);
   }
   block_barrier();  // every wave is done with the tile buffers, which the output slots reuse
 
@@ -399,7 +410,7 @@ __global__ __launch_bounds__(256, MINB) void attn_fwd_kernel(int B, int S, int h
 // permuted transpose read, which matches the token order of the dS^T
 // registers.  This kernel also writes D_i = dO_i . O_i for the dK/dV kernel.
 
-template <int D, int NW, int KT, int ST, int MINB>
+template <int D, int NW, int KT, int MINB>
 __global__ __launch_bounds__(NW * 64, MINB) void attn_bwd_dq_kernel(int B, int S, int heads,
                                                                     const bf16_t *__restrict__ qkv, uint32_t qkv_bytes,
                                                                     const bf16_t *__restrict__ o,
@@ -409,7 +420,6 @@ __global__ __launch_bounds__(NW * 64, MINB) void attn_bwd_dq_kernel(int B, int S
   using H = Head<D>;
   constexpr int TB = tile_bytes<KT>(), NL = TileLoads<KT, NW>::N;
   constexpr int ROWS = 32 * NW, STAGE = 2 * TB;  // K, V
-  static_assert(ST == 2 || ST == 3, "two or three tile stages");
   extern __shared__ __attribute__((aligned(1024))) char smem_raw[];
   const lds_char *smem = (const lds_char *)(smem_raw);
   const uint32_t lds0 = static_cast<uint32_t>(reinterpret_cast<uintptr_t>(smem));
@@ -434,7 +444,7 @@ __global__ __launch_bounds__(NW * 64, MINB) void attn_bwd_dq_kernel(int B, int S
   const uint32_t v_base = k_base + static_cast<uint32_t>(A * 2);
   const uint32_t tile_step = static_cast<uint32_t>(KT * ld * 2);
   auto issue = [&](int t) {
-    const uint32_t buf = lds0 + (t % ST) * STAGE;
+    const uint32_t buf = lds0 + (t & 1) * STAGE;
     const int rem = S - t * KT;
     tile_issue<KT, NW>(rsrc, buf, voff, k_base + t * tile_step, wid, lane, rem, ld, false);
     tile_issue<KT, NW>(rsrc, buf + TB, voff, v_base + t * tile_step, wid, lane, rem, ld, false);
@@ -461,15 +471,17 @@ __global__ __launch_bounds__(NW * 64, MINB) void attn_bwd_dq_kernel(int B, int S
   f32x16_t acc[H::NF];
 #pragma unroll
   for (int i = 0; i < H::NF; ++i) acc[i] = f32x16_t{};
-  constexpr int LOADS = 2 * NL;
   constexpr int NS = KT / 32;  // 32-key fragments per tile
   const int nk = (S + KT - 1) / KT;
-  for (int t = 0; t < ST - 1 && t < nk; ++t) issue(t);
-  for (int t = 0; t < nk; ++t) {
-    wait_tiles<LOADS>(min(nk - 1 - t, ST - 2));  // this wave's loads of tile t
+  // K: row reads for S^T and the permuted column reads; V (TB further): row reads
+  TileReads<D, true> rd;
+  rd.init(lane, 0, 0);
+  issue(0);
+  auto tile = [&](auto stage, int t) {
+    wait_vmcnt<0>();  // this wave's loads of tile t
     block_barrier();  // everyone's loads of tile t landed; tile t - 1's buffer is free
-    if (t + ST - 1 < nk) issue(t + ST - 1);
-    const lds_char *Ks = smem + (t % ST) * STAGE, *Vs = Ks + TB;
+    if (t + 1 < nk) issue(t + 1);
+    const lds_char *Ks = smem + stage.value * STAGE, *Vs = Ks + TB;
     const int k0 = t * KT;
     if (active) {  // waves whose queries all lie past the sequence only load and synchronise
     f32x16_t sv[NS], dp[NS];
@@ -479,8 +491,8 @@ __global__ __launch_bounds__(NW * 64, MINB) void attn_bwd_dq_kernel(int B, int S
       dp[f] = f32x16_t{};
 #pragma unroll
       for (int kk = 0; kk < H::KS; ++kk) {
-        sv[f] = mfma32(tile_rows(Ks, f * 32, kk, lane), qf[kk], sv[f]);
-        dp[f] = mfma32(tile_rows(Vs, f * 32, kk, lane), df[kk], dp[f]);
+        sv[f] = mfma32(rd.row(Ks, f, kk), qf[kk], sv[f]);
+        dp[f] = mfma32(rd.row(Vs, f, kk), df[kk], dp[f]);
       }
     }
 #pragma unroll
@@ -499,9 +511,13 @@ __global__ __launch_bounds__(NW * 64, MINB) void attn_bwd_dq_kernel(int B, int S
     for (int st = 0; st < KT / 16; ++st) {
       const bf16x8_t sb = pack8(sv[st >> 1], st & 1);
 #pragma unroll
-      for (int nf = 0; nf < H::NF; ++nf) acc[nf] = mfma32(tile_cols_perm(Ks, nf * 32, st, lane), sb, acc[nf]);
+      for (int nf = 0; nf < H::NF; ++nf) acc[nf] = mfma32(rd.col(Ks, nf, st), sb, acc[nf]);
     }
     }
+  };
+  for (int t = 0; t < nk; t += 2) {
+    tile(Stage<0>(), t);
+    if (t + 1 < nk) tile(Stage<1>(), t + 1);
   }
   block_barrier();  // the output slots reuse the tile buffers
   const int q0 = qt * ROWS + wid * 32;
@@ -599,24 +615,25 @@ __global__ __launch_bounds__(NG * 128, MINB) void attn_bwd_dkdv_kernel(int B, in
   const int pswz = (lane >> (NS == 1 ? 2 : 1)) & (4 * NS - 1);
   const float c = kLog2e / sqrtf(static_cast<float>(D));
   const int nq = (S + KT - 1) / KT;
+  // wave A: row reads of Q, column reads of dO; wave B the other way round
+  TileReads<D, true> reads;
+  reads.init(lane, role_a ? 0 : TB, role_a ? TB : 0);
   issue(0);
-  for (int t = 0; t < nq; ++t) {
+  auto tile = [&](auto stage, int t) {
     wait_vmcnt<0>();  // this wave's loads of tile t
     // every wave's loads of tile t have landed, and every wave is done with
     // tile t - 1: its buffer is refilled next and its P slots rewritten
     block_barrier();
     if (t + 1 < nq) issue(t + 1);
-    const lds_char *Qs = smem + (t & 1) * STAGE, *Ds = Qs + TB;
-    const float *Ls = reinterpret_cast<const float *>(smem_raw + (t & 1) * STAGE + TILES);
+    const lds_char *Ts = smem + stage.value * STAGE;
+    const float *Ls = reinterpret_cast<const float *>(smem_raw + stage.value * STAGE + TILES);
     const int q0 = t * KT;
     // S^T (wave A) or dP^T (wave B): register 4g+e of fragment f is query
     // f*32 + 8g + 4hf + e (four consecutive queries)
-    const lds_char *Rs = role_a ? Qs : Ds;
-    const lds_char *Cs = role_a ? Ds : Qs;
     // dO^T (wave A) or Q^T (wave B) operands of the token-contracting
     // product, read while S or dP and the P hand-over run
     ColOperands<D, KT, (D <= kPrefetchMaxD), true> cop;
-    if (active) cop.fetch(Cs, lane);
+    if (active) cop.fetch(Ts, reads);
     f32x16_t sv[NS];
     // waves whose keys all lie past the sequence only load and synchronise
     // (both waves of a key group agree)
@@ -625,7 +642,7 @@ __global__ __launch_bounds__(NG * 128, MINB) void attn_bwd_dkdv_kernel(int B, in
     for (int f = 0; f < NS; ++f) {
       sv[f] = f32x16_t{};
 #pragma unroll
-      for (int kk = 0; kk < H::KS; ++kk) sv[f] = mfma32(tile_rows(Rs, f * 32, kk, lane), rf[kk], sv[f]);
+      for (int kk = 0; kk < H::KS; ++kk) sv[f] = mfma32(reads.row(Ts, f, kk), rf[kk], sv[f]);
     }
     if (role_a) {
       // lse and D of queries past the sequence are not this sequence's: the
@@ -671,9 +688,13 @@ __global__ __launch_bounds__(NG * 128, MINB) void attn_bwd_dkdv_kernel(int B, in
     for (int st = 0; st < KT / 16; ++st) {
       const bf16x8_t pb = pack8(sv[st >> 1], st & 1);
 #pragma unroll
-      for (int nf = 0; nf < H::NF; ++nf) acc[nf] = mfma32(cop.get(Cs, nf, st, lane), pb, acc[nf]);
+      for (int nf = 0; nf < H::NF; ++nf) acc[nf] = mfma32(cop.get(Ts, reads, nf, st), pb, acc[nf]);
     }
     }
+  };
+  for (int t = 0; t < nq; t += 2) {
+    tile(Stage<0>(), t);
+    if (t + 1 < nq) tile(Stage<1>(), t + 1);
   }
   block_barrier();  // the output slots reuse the tile buffers
   // wave A holds dV, wave B dK
@@ -686,17 +707,17 @@ __global__ __launch_bounds__(NG * 128, MINB) void attn_bwd_dkdv_kernel(int B, in
 // NG groups of 32 keys, two waves each.  KT is the token tile streamed
 // through LDS, MINB the workgroups each CU must hold at once (it caps the
 // registers per wave: 512 / (waves per SIMD)).
-constexpr int kFwdKT = 32, kFwdStages = 2, kFwdMinBlocks = 3, kFwdSmallGrid = 256;
-constexpr int kDqWaves = 4, kDqKT = 32, kDqStages = 2, kDqMinBlocks = 2;
+constexpr int kFwdKT = 32, kFwdMinBlocks = 3, kFwdSmallGrid = 256;
+constexpr int kDqWaves = 4, kDqKT = 32, kDqMinBlocks = 2;
 constexpr int kDkvGroups = 2, kDkvKT = 32, kDkvMinBlocks = 3;
 
-template <int D, int KT, int ST, int MINB>
+template <int D, int KT, int MINB>
 void launch_fwd_cfg(int B, int S, int heads, const bf16_t *qkv, bf16_t *o, float *lse, hipStream_t s) {
   const int blocks = B * heads * ((S + kRows - 1) / kRows);
   const uint32_t bytes = static_cast<uint32_t>(static_cast<size_t>(B) * S * 3 * heads * D * 2);
-  // ST stages of (K, V) tiles; the per-wave 8 KB output slots reuse them
-  constexpr int lds = std::max(2 * ST * tile_bytes<KT>(), 4 * 8192);
-  hipLaunchKernelGGL((attn_fwd_kernel<D, KT, ST, MINB>), dim3(blocks), dim3(256), lds, s, B, S, heads, qkv, bytes, o,
+  // two stages of (K, V) tiles; the per-wave 8 KB output slots reuse them
+  constexpr int lds = std::max(4 * tile_bytes<KT>(), 4 * 8192);
+  hipLaunchKernelGGL((attn_fwd_kernel<D, KT, MINB>), dim3(blocks), dim3(256), lds, s, B, S, heads, qkv, bytes, o,
                      lse);
 }
 
@@ -708,9 +729,9 @@ template <int D>
 void launch_fwd_d(int B, int S, int heads, const bf16_t *qkv, bf16_t *o, float *lse, hipStream_t s) {
   const long blocks = static_cast<long>(B) * heads * ((S + kRows - 1) / kRows);
   if (blocks <= kFwdSmallGrid)
-    launch_fwd_cfg<D, 64, 2, 2>(B, S, heads, qkv, o, lse, s);
+    launch_fwd_cfg<D, 64, 2>(B, S, heads, qkv, o, lse, s);
   else
-    launch_fwd_cfg<D, kFwdKT, kFwdStages, kFwdMinBlocks>(B, S, heads, qkv, o, lse, s);
+    launch_fwd_cfg<D, kFwdKT, kFwdMinBlocks>(B, S, heads, qkv, o, lse, s);
 }
 
 template <int D>
@@ -720,13 +741,13 @@ void launch_bwd_d(int B, int S, int heads, const bf16_t *qkv, const bf16_t *o, c
   const uint32_t do_bytes = static_cast<uint32_t>(static_cast<size_t>(B) * S * heads * D * 2);
   const int qblocks = B * heads * ((S + 32 * kDqWaves - 1) / (32 * kDqWaves));
   const int kblocks = B * heads * ((S + 32 * kDkvGroups - 1) / (32 * kDkvGroups));
-  // dQ: kDqStages stages of (K, V) tiles, reused by the per-wave output slots.
+  // dQ: two stages of (K, V) tiles, reused by the per-wave output slots.
   // dK/dV: two stages of (Q, dO, lse, D) and one 32 x KT fp32 P slot per key
   // group, or the per-wave output slots if those need more.
-  constexpr int kDqLds = std::max(2 * kDqStages * tile_bytes<kDqKT>(), kDqWaves * 8192);
+  constexpr int kDqLds = std::max(4 * tile_bytes<kDqKT>(), kDqWaves * 8192);
   constexpr int kDkvLds = std::max(2 * dkdv_stage_bytes<kDkvKT>() + kDkvGroups * 32 * kDkvKT * 4,
                                    2 * kDkvGroups * 8192);
-  hipLaunchKernelGGL((attn_bwd_dq_kernel<D, kDqWaves, kDqKT, kDqStages, kDqMinBlocks>), dim3(qblocks), dim3(kDqWaves * 64),
+  hipLaunchKernelGGL((attn_bwd_dq_kernel<D, kDqWaves, kDqKT, kDqMinBlocks>), dim3(qblocks), dim3(kDqWaves * 64),
                      kDqLds, s, B, S, heads, qkv, qkv_bytes, o, lse, dO, dqkv, dvec);
   hipLaunchKernelGGL((attn_bwd_dkdv_kernel<D, kDkvGroups, kDkvKT, kDkvMinBlocks>), dim3(kblocks),
                      dim3(kDkvGroups * 128), kDkvLds, s, B, S, heads, qkv, qkv_bytes, lse, dO, do_bytes, dvec, dqkv);
