@@ -152,23 +152,34 @@ void saved_layout(const enc_cfg_t *c, enc_saved_layout_t *L) {
 
 // Backward workspace regions (offsets in bytes).
 struct BwdWs {
-  size_t du, dy2, dh, dO, dqkv, dy1, ln_part, dvec, wg, wg_bytes, total;
+  size_t du, dy2, dh, dO, dqkv, dy1, dvec;
+  size_t ln_part[2];  // column sums of LN1 and LN2, added by the last launch
+  // partials of the split weight gradients (W2, W1, Wo, Wqkv), added by the last launch
+  size_t wg[4], wg_bytes[4];
+  size_t dg, dg_bytes;  // partials of the input gradients, which use the region in turn
+  size_t total;
 };
 
-// Partial sums of the layer's split products (each GEMM uses the region in
-// turn): the largest need of the four weight gradients, the four input
-// gradients and the four forward projections.
-size_t layer_gemm_ws(const enc_cfg_t *c) {
+// Partial sums of the layer's split input gradients and forward projections
+// (each GEMM uses the region in turn): the largest need of the four of each.
+size_t layer_dgrad_fwd_ws(const enc_cfg_t *c) {
   const int M = c->batch * c->seq, H = c->hidden, A = c->heads * c->head_dim, F = c->mlp;
-  const size_t wg = std::max(std::max(gemm_wgrad_ws_bytes(H, F, M), gemm_wgrad_ws_bytes(F, H, M)),
-                             std::max(gemm_wgrad_ws_bytes(H, A, M), gemm_wgrad_ws_bytes(3 * A, H, M)));
   // input gradients: du [M, F] over H, dy2 [M, H] over F, dO [M, A] over H, dy1 [M, H] over 3A
   const size_t dg = std::max(std::max(gemm_ws_bytes(M, F, H), gemm_ws_bytes(M, H, F)),
                              std::max(gemm_ws_bytes(M, A, H), gemm_ws_bytes(M, H, 3 * A)));
   // forward: qkv [M, 3A] over H, h [M, H] over A, u [M, F] over H, out [M, H] over F
   const size_t fw = std::max(std::max(gemm_ws_bytes(M, 3 * A, H), gemm_ws_bytes(M, H, A)),
                              std::max(gemm_ws_bytes(M, F, H), gemm_ws_bytes(M, H, F)));
-  return std::max(wg, std::max(dg, fw));
+  return std::max(dg, fw);
+}
+
+// What the forward composite asks of a given workspace: the largest need of
+// any of the layer's split products.
+size_t layer_gemm_ws(const enc_cfg_t *c) {
+  const int M = c->batch * c->seq, H = c->hidden, A = c->heads * c->head_dim, F = c->mlp;
+  const size_t wg = std::max(std::max(gemm_wgrad_ws_bytes(H, F, M), gemm_wgrad_ws_bytes(F, H, M)),
+                             std::max(gemm_wgrad_ws_bytes(H, A, M), gemm_wgrad_ws_bytes(3 * A, H, M)));
+  return std::max(wg, layer_dgrad_fwd_ws(c));
 }
 
 BwdWs bwd_layout(const enc_cfg_t *c) {
@@ -187,10 +198,16 @@ BwdWs bwd_layout(const enc_cfg_t *c) {
   w.dO = take(M * A * 2);
   w.dqkv = take(M * 3 * A * 2);
   w.dy1 = take(M * H * 2);
-  w.ln_part = take(ln_bwd_ws_bytes(static_cast<int>(M), c->hidden));
+  for (size_t &part : w.ln_part) part = take(ln_bwd_ws_bytes(static_cast<int>(M), c->hidden));
   w.dvec = take(attn_bwd_ws_bytes(c->batch, c->seq, c->heads));
-  w.wg_bytes = layer_gemm_ws(c);
-  w.wg = take(w.wg_bytes);
+  const int iM = static_cast<int>(M), iH = c->hidden, iA = static_cast<int>(A), iF = c->mlp;
+  w.wg_bytes[0] = gemm_wgrad_ws_bytes(iH, iF, iM);
+  w.wg_bytes[1] = gemm_wgrad_ws_bytes(iF, iH, iM);
+  w.wg_bytes[2] = gemm_wgrad_ws_bytes(iH, iA, iM);
+  w.wg_bytes[3] = gemm_wgrad_ws_bytes(3 * iA, iH, iM);
+  for (int i = 0; i < 4; ++i) w.wg[i] = take(w.wg_bytes[i]);
+  w.dg_bytes = layer_dgrad_fwd_ws(c);
+  w.dg = take(w.dg_bytes);
   w.total = off;
   return w;
 }
@@ -255,12 +272,12 @@ bool gemm_dgrad_add(int M, int N, int K, const bf16_t *dY, const bf16_t *W, cons
 
 // dW[N, K] (+)= dY[M, N]^T X[M, K]; db[N] (+)= sum_m dY
 bool gemm_wgrad(int M, int N, int K, const bf16_t *dY, const bf16_t *X, float *dW, float *db, int acc, void *ws,
-                size_t ws_bytes, hipStream_t s) {
+                size_t ws_bytes, hipStream_t s, FinishJobs *defer = nullptr) {
   GemmArgs a{};
   a.M = N, a.N = K, a.K = M;
   a.A = dY, a.lda = N, a.B = X, a.ldb = K;
   a.Wf = dW, a.ldy = K, a.db = db, a.accumulate = acc;
-  return launch_gemm_wgrad(a, ws, ws_bytes, s);
+  return launch_gemm_wgrad(a, ws, ws_bytes, s, defer);
 }
 
 int linear_dims(const char *fn, int M, std::initializer_list<int> feats) {
@@ -835,20 +852,25 @@ int encoder_layer_bwd(const enc_cfg_t *cfg, const enc_params_t *params, const en
   const float *mean2 = at<float>(saved, L.mean2), *rstd2 = at<float>(saved, L.rstd2);
   bf16_t *du = at<bf16_t>(ws, W.du), *dy2 = at<bf16_t>(ws, W.dy2), *dh = at<bf16_t>(ws, W.dh);
   bf16_t *dO = at<bf16_t>(ws, W.dO), *dqkv = at<bf16_t>(ws, W.dqkv), *dy1 = at<bf16_t>(ws, W.dy1);
-  float *part = at<float>(ws, W.ln_part), *dvec = at<float>(ws, W.dvec);
-  void *wg = W.wg_bytes ? at<char>(ws, W.wg) : nullptr;  // split weight-gradient partials
+  float *part1 = at<float>(ws, W.ln_part[0]), *part2 = at<float>(ws, W.ln_part[1]), *dvec = at<float>(ws, W.dvec);
+  void *dg = W.dg_bytes ? at<char>(ws, W.dg) : nullptr;  // split input-gradient partials
+  void *wg[4];                                           // split weight-gradient partials
+  for (int i = 0; i < 4; ++i) wg[i] = W.wg_bytes[i] ? at<char>(ws, W.wg[i]) : nullptr;
 
-  bool okk = gemm_dgrad(M, H, F, dout, p.w_2, u, du, wg, W.wg_bytes, s);      // du = dout W2 * GELU'(u)
-  okk = okk && gemm_wgrad(M, H, F, dout, g, gr.w_2, gr.b_2, acc, wg, W.wg_bytes, s);          // dW2, db2
-  okk = okk && gemm_dgrad(M, F, H, du, p.w_1, nullptr, dy2, wg, W.wg_bytes, s);  // dy2 = du W1
-  okk = okk && gemm_wgrad(M, F, H, du, y2, gr.w_1, gr.b_1, acc, wg, W.wg_bytes, s);           // dW1, db1
-  okk = okk && launch_ln_bwd(M, H, dy2, h, mean2, rstd2, p.ln2_g, dout, dh, gr.ln2_g, gr.ln2_b, acc, part, s);
-  okk = okk && gemm_dgrad(M, H, A, dh, p.w_o, nullptr, dO, wg, W.wg_bytes, s);   // dO = dh Wo
-  okk = okk && gemm_wgrad(M, H, A, dh, o, gr.w_o, gr.b_o, acc, wg, W.wg_bytes, s);            // dWo, dbo
+  FinishJobs fin;  // the fixed-order sums of partials, in one launch at the end
+  bool okk = gemm_dgrad(M, H, F, dout, p.w_2, u, du, dg, W.dg_bytes, s);  // du = dout W2 * GELU'(u)
+  okk = okk && gemm_wgrad(M, H, F, dout, g, gr.w_2, gr.b_2, acc, wg[0], W.wg_bytes[0], s, &fin);  // dW2, db2
+  okk = okk && gemm_dgrad(M, F, H, du, p.w_1, nullptr, dy2, dg, W.dg_bytes, s);  // dy2 = du W1
+  okk = okk && gemm_wgrad(M, F, H, du, y2, gr.w_1, gr.b_1, acc, wg[1], W.wg_bytes[1], s, &fin);  // dW1, db1
+  okk = okk &&
+        launch_ln_bwd(M, H, dy2, h, mean2, rstd2, p.ln2_g, dout, dh, gr.ln2_g, gr.ln2_b, acc, part2, s, &fin);
+  okk = okk && gemm_dgrad(M, H, A, dh, p.w_o, nullptr, dO, dg, W.dg_bytes, s);  // dO = dh Wo
+  okk = okk && gemm_wgrad(M, H, A, dh, o, gr.w_o, gr.b_o, acc, wg[2], W.wg_bytes[2], s, &fin);  // dWo, dbo
   okk = okk && launch_attn_bwd(cfg->batch, cfg->seq, cfg->heads, cfg->head_dim, qkv, o, lse, dO, dqkv, dvec, s);
-  okk = okk && gemm_dgrad(M, 3 * A, H, dqkv, p.w_qkv, nullptr, dy1, wg, W.wg_bytes, s);  // dy1 = dqkv Wqkv
-  okk = okk && gemm_wgrad(M, 3 * A, H, dqkv, y1, gr.w_qkv, gr.b_qkv, acc, wg, W.wg_bytes, s);  // dWqkv, dbqkv
-  okk = okk && launch_ln_bwd(M, H, dy1, x, mean1, rstd1, p.ln1_g, dh, dx, gr.ln1_g, gr.ln1_b, acc, part, s);
+  okk = okk && gemm_dgrad(M, 3 * A, H, dqkv, p.w_qkv, nullptr, dy1, dg, W.dg_bytes, s);  // dy1 = dqkv Wqkv
+  okk = okk && gemm_wgrad(M, 3 * A, H, dqkv, y1, gr.w_qkv, gr.b_qkv, acc, wg[3], W.wg_bytes[3], s, &fin);  // dWqkv
+  okk = okk && launch_ln_bwd(M, H, dy1, x, mean1, rstd1, p.ln1_g, dh, dx, gr.ln1_g, gr.ln1_b, acc, part1, s, &fin);
+  okk = okk && launch_finish(fin, s);
   if (!okk) return refused_after_checks(fn);
   return launched(fn);
 }

@@ -32,6 +32,7 @@
 #include "common.hpp"
 #include "kernels.hpp"
 #include "lds_dma.hpp"
+#include "reduce.hpp"
 
 namespace optimus {
 
@@ -1421,9 +1422,7 @@ bool launch_gemm_dgrad(const GemmArgs &a, Epi epi, void *ws, size_t ws_bytes, hi
 
 namespace {
 
-// out[i] = (accumulate ? out[i] : 0) + part[0][i] + part[1][i] + ... in split
-// order (deterministic), over n4 float4s; blockIdx.y picks the dW or the db
-// segment.
+// The split sum of dW (blockIdx.y 0) or db (1), over n4 float4s.
 __global__ __launch_bounds__(256) void splitk_reduce_kernel(float *__restrict__ w, const float *__restrict__ wp,
                                                             long w4, float *__restrict__ b,
                                                             const float *__restrict__ bp, long b4, int splits,
@@ -1431,16 +1430,13 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(float *__restrict__ 
   float *out = blockIdx.y == 0 ? w : b;
   const float *part = blockIdx.y == 0 ? wp : bp;
   const long n4 = blockIdx.y == 0 ? w4 : b4;
-  for (long i = blockIdx.x * 256L + threadIdx.x; i < n4; i += static_cast<long>(gridDim.x) * 256) {
-    f32x4_t v = accumulate ? reinterpret_cast<const f32x4_t *>(out)[i] : f32x4_t{0.f, 0.f, 0.f, 0.f};
-    for (int sp = 0; sp < splits; ++sp) v += reinterpret_cast<const f32x4_t *>(part)[sp * n4 + i];
-    reinterpret_cast<f32x4_t *>(out)[i] = v;
-  }
+  for (long i = blockIdx.x * 256L + threadIdx.x; i < n4; i += static_cast<long>(gridDim.x) * 256)
+    split_sum_at(i, n4, out, part, splits, accumulate);
 }
 
 }  // namespace
 
-bool launch_gemm_wgrad(const GemmArgs &a, void *ws, size_t ws_bytes, hipStream_t s) {
+bool launch_gemm_wgrad(const GemmArgs &a, void *ws, size_t ws_bytes, hipStream_t s, FinishJobs *defer) {
   // both paths fuse the bias gradient into the weight-gradient kernel
   const SplitPlan sp = wgrad_split_plan(a.M, a.N, a.K);
   if (sp.splits > 1 && ws != nullptr && ws_bytes >= gemm_wgrad_ws_bytes(a.M, a.N, a.K) && a.ldy == a.N &&
@@ -1455,6 +1451,9 @@ bool launch_gemm_wgrad(const GemmArgs &a, void *ws, size_t ws_bytes, hipStream_t
     b.accumulate = 0;
     if (launch_lds<true, true, Epi::kF32>(b, s, sp.tile)) {
       const long w4 = static_cast<long>(a.M) * a.N / 4, b4 = a.db ? a.M / 4 : 0;
+      if (defer)
+        return defer->add_split(a.Wf, b.Wf, w4, sp.splits, a.accumulate) &&
+               (!a.db || defer->add_split(a.db, b.db, b4, sp.splits, a.accumulate));
       const int blocks = static_cast<int>(std::min<long>((w4 + 255) / 256, 2048));
       hipLaunchKernelGGL(splitk_reduce_kernel, dim3(blocks, a.db ? 2 : 1), dim3(256), 0, s, a.Wf, b.Wf, w4, a.db,
                          b.db, b4, sp.splits, a.accumulate);

@@ -13,12 +13,34 @@ namespace optimus {
 
 typedef uint16_t bf16_t;
 
+// ---- Reductions deferred to the end of a layer's backward.  A launcher given
+// a FinishJobs leaves its fixed-order sum of partials there instead of
+// launching it; launch_finish then runs them all in one grid.  The partials
+// must stay untouched until it has.
+struct FinishJob {
+  float *out;
+  const float *part;
+  long n4;          // float4s per partial (split sums)
+  int parts, cols;  // partials; columns of a row of them (column sums), else 0
+  int accumulate, first_block;
+};
+
+struct FinishJobs {
+  static constexpr int kMax = 12;  // four weight gradients with their biases, two LayerNorms
+  FinishJob job[kMax];
+  int n = 0, blocks = 0;
+  bool add_split(float *out, const float *part, long n4, int splits, int accumulate);
+  bool add_columns(float *out, const float *part, int rows, int cols, int accumulate);
+};
+
+bool launch_finish(const FinishJobs &jobs, hipStream_t s);
+
 // ---- LayerNorm
 bool launch_ln_fwd(int rows, int cols, const bf16_t *x, const bf16_t *gamma, const bf16_t *beta, float eps,
                    bf16_t *y, float *mean, float *rstd, hipStream_t s);
 bool launch_ln_bwd(int rows, int cols, const bf16_t *dy, const bf16_t *x, const float *mean, const float *rstd,
                    const bf16_t *gamma, const bf16_t *dresid, bf16_t *dx, float *dgamma, float *dbeta,
-                   int accumulate, float *part, hipStream_t s);
+                   int accumulate, float *part, hipStream_t s, FinishJobs *defer = nullptr);
 
 // ---- GEMM family: C[m, n] = sum_k A(m, k) B(n, k)
 enum class Epi : int {
@@ -66,7 +88,7 @@ bool launch_gemm_dgrad(const GemmArgs &a, Epi epi, void *ws, size_t ws_bytes, hi
 // whose output tiles leave most CUs idle splits the token contraction over
 // several workgroups per tile and adds the fp32 partials in a fixed order;
 // ws = nullptr never splits.
-bool launch_gemm_wgrad(const GemmArgs &a, void *ws, size_t ws_bytes, hipStream_t s);
+bool launch_gemm_wgrad(const GemmArgs &a, void *ws, size_t ws_bytes, hipStream_t s, FinishJobs *defer = nullptr);
 
 // ---- QK normalisation (LayerNorm of every query and key vector over head_dim)
 bool launch_qk_norm_fwd(int M, int heads, int d, const bf16_t *qkv, const bf16_t *qg, const bf16_t *qb,

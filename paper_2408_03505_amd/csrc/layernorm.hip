@@ -11,6 +11,7 @@
 // partials, so dgamma and dbeta are deterministic.
 #include "common.hpp"
 #include "kernels.hpp"
+#include "reduce.hpp"
 
 namespace optimus {
 
@@ -319,44 +320,13 @@ __global__ __launch_bounds__(kThreads) void ln_bwd_kernel(int rows, int cols, in
 }
 
 // dgamma (blockIdx.y 0) or dbeta (1) (+)= the fixed-order sum of the nblk
-// partial rows.  Block = 64 columns (8 chunks of 8) x 32 groups of partial
-// rows; the 32 group sums are added in a fixed order through LDS.
-constexpr int kRedCols = 64, kRedGroups = 32;
-
+// partial rows.
 __global__ __launch_bounds__(kThreads) void ln_bwd_reduce_kernel(int nblk, int cols, const float *__restrict__ part,
                                                                  float *__restrict__ dgamma,
                                                                  float *__restrict__ dbeta, int accumulate) {
   __shared__ float red[kRedGroups][kRedCols + 1];
-  const int chunk = threadIdx.x & 7, grp = threadIdx.x >> 3;
-  const int c0 = blockIdx.x * kRedCols + chunk * 8;
-  const float *src = part + static_cast<size_t>(blockIdx.y) * nblk * cols;
-  float v[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-  if (c0 < cols) {
-#pragma unroll 4
-    for (int b = grp; b < nblk; b += kRedGroups) {
-      const float *q = src + static_cast<size_t>(b) * cols + c0;
-      const f32x4_t a = *reinterpret_cast<const f32x4_t *>(q);
-      const f32x4_t c = *reinterpret_cast<const f32x4_t *>(q + 4);
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        v[e] += a[e];
-        v[4 + e] += c[e];
-      }
-    }
-  }
-#pragma unroll
-  for (int e = 0; e < 8; ++e) red[grp][chunk * 8 + e] = v[e];
-  __syncthreads();
-  if (threadIdx.x < kRedCols) {
-    const int col = blockIdx.x * kRedCols + threadIdx.x;
-    float tsum = 0.f;
-#pragma unroll 8
-    for (int q = 0; q < kRedGroups; ++q) tsum += red[q][threadIdx.x];
-    if (col < cols) {
-      float *out = blockIdx.y == 0 ? dgamma : dbeta;
-      out[col] = accumulate ? out[col] + tsum : tsum;
-    }
-  }
+  column_sum_block(blockIdx.x, nblk, cols, part + static_cast<size_t>(blockIdx.y) * nblk * cols,
+                   blockIdx.y == 0 ? dgamma : dbeta, accumulate, red);
 }
 
 }  // namespace
@@ -394,7 +364,7 @@ bool launch_ln_fwd(int rows, int cols, const bf16_t *x, const bf16_t *gamma, con
 
 bool launch_ln_bwd(int rows, int cols, const bf16_t *dy, const bf16_t *x, const float *mean, const float *rstd,
                    const bf16_t *gamma, const bf16_t *dresid, bf16_t *dx, float *dgamma, float *dbeta,
-                   int accumulate, float *part, hipStream_t s) {
+                   int accumulate, float *part, hipStream_t s, FinishJobs *defer) {
   const int nch = cols >> 3;
   const int tpr = ln_bwd_tpr(cols);
   const int rpb = ln_bwd_rows_per_block(rows, cols);
@@ -427,6 +397,9 @@ bool launch_ln_bwd(int rows, int cols, const bf16_t *dy, const bf16_t *x, const 
     else OPT_LN_BWD(64, 4);
   }
 #undef OPT_LN_BWD
+  if (defer)
+    return defer->add_columns(dgamma, part, nblk, cols, accumulate) &&
+           defer->add_columns(dbeta, part + static_cast<size_t>(nblk) * cols, nblk, cols, accumulate);
   hipLaunchKernelGGL(ln_bwd_reduce_kernel, dim3((cols + kRedCols - 1) / kRedCols, 2), dim3(kThreads), 0, s, nblk, cols,
                      part, dgamma, dbeta, accumulate);
   return true;
