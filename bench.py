@@ -219,7 +219,8 @@ TRAFFIC_MD = os.path.join(ROOT, "profiles", "vit22b_layer_hbm_traffic.md")
 # argument structs they receive and the launch geometry): traffic counters
 # describe these files only.
 _COMMON_SRC = ("common.hpp", "lds_dma.hpp", "kernels.hpp", "geometry.hpp")
-_FAMILY_SRC = {"gemm": ("gemm.hip",), "attention": ("attention.hip",), "layernorm": ("layernorm.hip",)}
+_FAMILY_SRC = {"gemm": ("gemm.hip", "reduce.hpp"), "attention": ("attention.hip",),
+               "layernorm": ("layernorm.hip", "reduce.hpp")}
 
 
 def entry_family(entry):

@@ -4,20 +4,18 @@
 //   C[m, n] = sum_k A(m, k) * B(n, k),  fp32 accumulation on
 //   v_mfma_f32_16x16x32_bf16 (32x32x16 in the register-staged kernel).
 //
-// Operands whose contraction index is contiguous in memory (activations in
-// the forward, weights [out, in] in the forward) are copied to LDS with
-// 16-byte loads.  Operands whose contraction index is strided (the weight in
-// the input gradient, both operands of the weight gradient) are read as 8x8
-// bf16 blocks, transposed in registers with v_perm_b32 and written to LDS so
-// that every LDS tile is [row][k] with k contiguous; all MFMA operand reads
-// are then 16-byte ds_read_b128 from rows padded by 16 bytes (conflict-free
-// for 8 consecutive lanes).  Tiles are double-buffered in LDS with one
-// barrier per k-step; the next tile's global loads are issued before the
-// current tile's MFMAs.
+// Three families.  gemm_half_kernel (256-row tiles) and gemm_ring_kernel
+// (smaller tiles) copy tiles straight to LDS: operands whose contraction index
+// is contiguous in memory as [row][k], read with ds_read_b128; strided ones
+// (the weight in the input gradient, both operands of the weight gradient) as
+// they lie, [k][row], read with the transposing ds_read_b64_tr_b16.
+// gemm_kernel takes what they don't (contiguous contractions that are no
+// multiple of 64, operands of 4 GiB and more): it stages through registers,
+// transposing strided operands as 8x8 bf16 blocks with v_perm_b32, into
+// [row][k] tiles of rows padded by 16 bytes, double-buffered.
 //
-// The MFMA is issued as D = Btile * Atile^T so that each lane of the 32x32
-// result owns one output row m and four consecutive output columns n: the
-// bf16 epilogue stores 8 bytes and the fp32 epilogue 16 bytes per access.
+// The MFMA is issued as D = Btile * Atile^T so that each lane owns one output
+// row m and runs of four consecutive output columns n.
 // Epilogues fuse bias, residual, GELU (writing both pre- and post-activation),
 // GELU' (for the MLP input gradient) and, for weight gradients, the bias
 // gradient as row sums of the transposed A operand (deterministic).
@@ -533,8 +531,8 @@ __global__ __launch_bounds__(WM *WN * 64) void gemm_kernel(GemmArgs p) {
 // Direct-to-LDS pipeline (the large-problem path).
 //
 // Tiles go from HBM straight into LDS with buffer_load_dwordx4 ... lds (no
-// staging registers), STAGES deep, so the loads for k-step t+STAGES-1 are in
-// flight while k-step t runs on the MFMAs.  The buffer resource bounds every
+// staging registers), some k-steps ahead of the MFMAs that read them (each
+// pipeline below says how many).  The buffer resource bounds every
 // operand tensor: rows past its end (tokens past M, weight rows past N, or
 // contraction rows past K of a transposed operand) read as zero.
 //
@@ -542,18 +540,15 @@ __global__ __launch_bounds__(WM *WN * 64) void gemm_kernel(GemmArgs p) {
 //  - contraction-contiguous operand: [row][BK], chunk c of row r stored at
 //    c ^ ((r / RP) % CPR) (RP rows share one 128-byte line); MFMA operands
 //    are single ds_read_b128.
-//  - contraction-strided operand: [BK][ROWS] exactly as in memory, chunk j of
-//    k-row k stored at j ^ 2*(k % 4); MFMA operands are two
-//    ds_read_b64_tr_b16, whose 16-lane transpose delivers lane l the column
-//    (l % 32) of k-rows 8*(l/32) + 0..7.
+//  - contraction-strided operand: [BK][ROWS] exactly as in memory, its
+//    chunks swizzled by t_swz; MFMA operands are two ds_read_b64_tr_b16, whose
+//    16-lane transpose delivers a lane one column of consecutive k-rows.
 // ===========================================================================
 
 // LDS is 64 banks x 4 bytes (256 bytes per cycle); a 16-lane quarter-wave
 // of ds_read_b128 and a half-wave of ds_read_b64_tr_b16 must hit distinct
 // banks.  nt tiles: RP rows share one 256-byte bank line, so chunk c of row
-// r goes to c ^ ((r / RP) % CPR).  Transposed tiles: k-rows are padded to a
-// power of two (TROWS) and chunk j of k-row k goes to j ^ 4 * (k % 4), which
-// spreads the four k-rows read together over four disjoint 64-byte ranges.
+// r goes to c ^ ((r / RP) % CPR).  Transposed tiles: t_swz below.
 template <int BK>
 struct NtTile {
   static constexpr int RB = BK * 2;                          // bytes per row
@@ -1264,11 +1259,8 @@ bool launch_ring_cfg(const GemmArgs &a, uint32_t a_bytes, uint32_t b_bytes, hipS
   return true;
 }
 
-// Direct-to-LDS path: pick the tile that minimises (rounds of 256 CUs) x
-// (tile area / per-tile efficiency).  256x256 tiles are the most efficient per
-// tile, 256x192 tiles divide the 6144- and 18432-wide outputs into whole
-// rounds; both run gemm_half_kernel.  128x128 tiles serve small problems
-// (gemm_lds_kernel, BK 64, two stages, two workgroups per CU).
+// Direct-to-LDS path on tile t (of kTiles): 256-row tiles run gemm_half_kernel,
+// the others gemm_ring_kernel.
 // Returns false when the operands do not fit the path's constraints.
 template <bool AT, bool BT, Epi EPI>
 bool launch_lds(const GemmArgs &a, hipStream_t s, TileShape t) {
