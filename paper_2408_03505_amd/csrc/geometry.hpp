@@ -142,10 +142,22 @@ struct SplitPlan {
   TileShape tile;
 };
 
+// Longest split of a weight gradient (tokens): that of a grid of 128x128
+// workgroups, two to a CU.  dW is returned in fp32, and the error of a sum
+// against 64 bits grows with its length: 1.3e-7 (2-norm, relative) in splits of
+// 512 tokens, 1.9e-7 of 1024, 2.7e-7 of 2048.  The cost model alone would save
+// the partials' traffic by summing twice as long.
+inline int wgrad_max_chunk(int M, int N, int K) {
+  const long tiles = static_cast<long>((M + 127) / 128) * ((N + 127) / 128);
+  const int s = static_cast<int>(std::min<long>(512 / tiles, std::min(K / kMinSplitTokens, kMaxSplits)));
+  return ((K + s - 1) / s + 63) / 64 * 64;
+}
+
 inline SplitPlan best_split(int M, int N, int K, GemmLayout l) {
   SplitPlan best{1, K, {0, 0}};
   float best_us = 0.f;
   const int max_s = std::min(K / kMinSplitTokens, kMaxSplits);
+  const int max_chunk = l == kWgrad ? wgrad_max_chunk(M, N, K) : K;
   for (const TileCost &t : kTiles) {
     const bool small = t.bm * t.bn < 128 * 128;
     if (l == kWgrad ? t.bm < 128 : !small && (t.bm != 128 || t.bn != 128)) continue;
@@ -153,7 +165,7 @@ inline SplitPlan best_split(int M, int N, int K, GemmLayout l) {
     for (int s = 2; s <= max_s && (s == 2 || n * s <= 1024); ++s) {
       if (l != kWgrad && small && n * s <= 256) continue;
       const int kc = ((K + s - 1) / s + 63) / 64 * 64;
-      if ((K + kc - 1) / kc != s) continue;
+      if ((K + kc - 1) / kc != s || kc > max_chunk) continue;
       const float us = gemm_cost(t, l, n * s, kc / 64) +
                        static_cast<float>(s + 1) * static_cast<float>(M) * static_cast<float>(N) * (4.f / 4.5e6f);
       if (best.splits == 1 || us < best_us) {
