@@ -148,8 +148,9 @@ int encoder_layer_fwd(const enc_cfg_t *cfg, const enc_params_t *params,
 
 /* Backward of encoder_layer_fwd given dout = dL/dout [M, H]: writes
  * dx [M, H] and the twelve parameter gradients (overwritten when
- * accumulate=0, added to when accumulate=1).  saved is the buffer the
- * forward filled for the same x and params. */
+ * accumulate=0, added to when accumulate=1).  Gradient buffers may share
+ * memory (tied parameters): they are then written in the chain's order.  saved
+ * is the buffer the forward filled for the same x and params. */
 int encoder_layer_bwd(const enc_cfg_t *cfg, const enc_params_t *params,
                       const enc_bf16 *x, const void *saved,
                       const enc_bf16 *dout, enc_bf16 *dx,

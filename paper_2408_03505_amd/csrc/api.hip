@@ -239,6 +239,26 @@ int check_grads(const char *fn, const enc_grads_t *g) {
   return c.code;
 }
 
+// Whether any two of a layer backward's outputs share memory.  Its deferred
+// sums run as blocks of one grid, in no order among themselves or after the
+// kernels that write in the chain, which is only the same when they don't.
+bool layer_outputs_overlap(const enc_cfg_t *c, const enc_grads_t &g, const enc_bf16 *dx) {
+  const size_t M = static_cast<size_t>(c->batch) * c->seq;
+  const size_t H = c->hidden, A = static_cast<size_t>(c->heads) * c->head_dim, F = c->mlp;
+  const struct {
+    const void *p;
+    size_t bytes;
+  } out[] = {{g.ln1_g, H * 4}, {g.ln1_b, H * 4}, {g.w_qkv, 3 * A * H * 4}, {g.b_qkv, 3 * A * 4}, {g.w_o, H * A * 4},
+             {g.b_o, H * 4},   {g.ln2_g, H * 4}, {g.ln2_b, H * 4},         {g.w_1, F * H * 4},   {g.b_1, F * 4},
+             {g.w_2, H * F * 4}, {g.b_2, H * 4}, {dx, M * H * 2}};
+  for (const auto &a : out)
+    for (const auto *b = out; b != &a; ++b) {
+      const uintptr_t x = reinterpret_cast<uintptr_t>(a.p), y = reinterpret_cast<uintptr_t>(b->p);
+      if (x < y ? y - x < a.bytes : x - y < b->bytes) return true;
+    }
+  return false;
+}
+
 // ---- unchecked launch helpers shared by the per-kernel entry points and the chains
 
 bool gemm_fwd(int M, int N, int K, const bf16_t *X, const bf16_t *W, const bf16_t *bias, const bf16_t *R, bf16_t *Y,
@@ -857,20 +877,22 @@ int encoder_layer_bwd(const enc_cfg_t *cfg, const enc_params_t *params, const en
   void *wg[4];                                           // split weight-gradient partials
   for (int i = 0; i < 4; ++i) wg[i] = W.wg_bytes[i] ? at<char>(ws, W.wg[i]) : nullptr;
 
-  FinishJobs fin;  // the fixed-order sums of partials, in one launch at the end
+  FinishJobs jobs;  // the fixed-order sums of partials, in one launch at the end
+  // outputs that share memory are written and added to in the chain's order
+  FinishJobs *fin = layer_outputs_overlap(cfg, gr, dx) ? nullptr : &jobs;
   bool okk = gemm_dgrad(M, H, F, dout, p.w_2, u, du, dg, W.dg_bytes, s);  // du = dout W2 * GELU'(u)
-  okk = okk && gemm_wgrad(M, H, F, dout, g, gr.w_2, gr.b_2, acc, wg[0], W.wg_bytes[0], s, &fin);  // dW2, db2
+  okk = okk && gemm_wgrad(M, H, F, dout, g, gr.w_2, gr.b_2, acc, wg[0], W.wg_bytes[0], s, fin);  // dW2, db2
   okk = okk && gemm_dgrad(M, F, H, du, p.w_1, nullptr, dy2, dg, W.dg_bytes, s);  // dy2 = du W1
-  okk = okk && gemm_wgrad(M, F, H, du, y2, gr.w_1, gr.b_1, acc, wg[1], W.wg_bytes[1], s, &fin);  // dW1, db1
+  okk = okk && gemm_wgrad(M, F, H, du, y2, gr.w_1, gr.b_1, acc, wg[1], W.wg_bytes[1], s, fin);  // dW1, db1
   okk = okk &&
-        launch_ln_bwd(M, H, dy2, h, mean2, rstd2, p.ln2_g, dout, dh, gr.ln2_g, gr.ln2_b, acc, part2, s, &fin);
+        launch_ln_bwd(M, H, dy2, h, mean2, rstd2, p.ln2_g, dout, dh, gr.ln2_g, gr.ln2_b, acc, part2, s, fin);
   okk = okk && gemm_dgrad(M, H, A, dh, p.w_o, nullptr, dO, dg, W.dg_bytes, s);  // dO = dh Wo
-  okk = okk && gemm_wgrad(M, H, A, dh, o, gr.w_o, gr.b_o, acc, wg[2], W.wg_bytes[2], s, &fin);  // dWo, dbo
+  okk = okk && gemm_wgrad(M, H, A, dh, o, gr.w_o, gr.b_o, acc, wg[2], W.wg_bytes[2], s, fin);  // dWo, dbo
   okk = okk && launch_attn_bwd(cfg->batch, cfg->seq, cfg->heads, cfg->head_dim, qkv, o, lse, dO, dqkv, dvec, s);
   okk = okk && gemm_dgrad(M, 3 * A, H, dqkv, p.w_qkv, nullptr, dy1, dg, W.dg_bytes, s);  // dy1 = dqkv Wqkv
-  okk = okk && gemm_wgrad(M, 3 * A, H, dqkv, y1, gr.w_qkv, gr.b_qkv, acc, wg[3], W.wg_bytes[3], s, &fin);  // dWqkv
-  okk = okk && launch_ln_bwd(M, H, dy1, x, mean1, rstd1, p.ln1_g, dh, dx, gr.ln1_g, gr.ln1_b, acc, part1, s, &fin);
-  okk = okk && launch_finish(fin, s);
+  okk = okk && gemm_wgrad(M, 3 * A, H, dqkv, y1, gr.w_qkv, gr.b_qkv, acc, wg[3], W.wg_bytes[3], s, fin);  // dWqkv
+  okk = okk && launch_ln_bwd(M, H, dy1, x, mean1, rstd1, p.ln1_g, dh, dx, gr.ln1_g, gr.ln1_b, acc, part1, s, fin);
+  okk = okk && launch_finish(jobs, s);
   if (!okk) return refused_after_checks(fn);
   return launched(fn);
 }

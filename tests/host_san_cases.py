@@ -10,6 +10,7 @@ would launch kernels on these pointers.
 """
 
 import ctypes
+import math
 
 import pytest
 
@@ -113,3 +114,37 @@ def test_linear_plan_queries():
             _ok("enc_linear_plan", layout, M, N, K, ctypes.byref(r), ctypes.byref(c), ctypes.byref(sp))
             assert r.value in (128, 256) and c.value in (128, 192, 256) and 1 <= sp.value <= 16
     assert L.enc_linear_plan(9, 16, 8, 8, ctypes.byref(r), ctypes.byref(c), ctypes.byref(sp)) == B.ENC_ERR_INVALID
+
+
+def test_layer_backward_defers_its_sums_only_into_distinct_outputs():
+    # tied gradients (one buffer for two of them, or overlapping ones) were
+    # always added up in the chain's order: nothing may be deferred then
+    cfg = CFGS[1]
+    c = B.make_cfg(cfg)
+    M, H = cfg["batch"] * cfg["seq"], cfg["hidden"]
+    params = B.EncParams(*[0x10000] * 12)
+    sizes = [4 * n for n in (math.prod(s) for s in B.param_shapes(cfg).values())]
+    base, ptrs = 0x1000000, []
+    for n in sizes + [2 * M * H]:  # the gradients and dx, end to end
+        ptrs.append(base)
+        base += n
+
+    def deferred(ptrs):
+        L.enc_host_stub_deferred()
+        grads = B.EncGrads(*ptrs[:12])
+        _ok("encoder_layer_bwd", ctypes.byref(c), ctypes.byref(params), P, P, P, ctypes.c_void_p(ptrs[12]),
+            ctypes.byref(grads), 1, P, B.layer_workspace_bytes(cfg), S0)
+        return L.enc_host_stub_deferred()
+
+    assert deferred(ptrs) == 6  # four weight gradients, two LayerNorms
+    assert deferred([p + 64 for p in ptrs]) == 6
+    order = list(B.PARAM_ORDER)
+    for a, b in (("ln1_g", "ln2_g"), ("ln1_b", "ln2_b"), ("b_o", "b_2"), ("w_1", "w_2"), ("b_o", "w_qkv")):
+        tied = list(ptrs)
+        tied[order.index(a)] = ptrs[order.index(b)]
+        assert deferred(tied) == 0, (a, b)
+    for i in range(13):  # one buffer reaches 16 bytes into the next, or starts 16 bytes early
+        if i < 12:
+            assert deferred(ptrs[:i] + [ptrs[i] + 16] + ptrs[i + 1:]) == 0, i
+        if i > 0:
+            assert deferred(ptrs[:i] + [ptrs[i] - 16] + ptrs[i + 1:]) == 0, i
