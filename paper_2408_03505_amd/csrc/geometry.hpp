@@ -57,19 +57,26 @@ inline size_t attn_bwd_ws_bytes(int B, int S, int heads) {
 // tiles; per_cu workgroups of a tile share a CU.  cost[kind] is the time in us
 // of one workgroup per 64-wide k-step and on top of them (prologue, epilogue):
 // {step, rest} alone on its CU and, where two share a CU, {step, rest} of such
-// a pair.  Fitted to 28 products per layout (ViT-Tiny to ViT-10B and the
-// ViT-22B shard: outputs 192 to 16384 wide, contractions 192 to 16384, every
-// tile timed on each): the fit is within 3-8% of the measured times on
-// average, and the tiles it picks took 1.5% longer in total than the best tile
-// of each product, 18% less than the rule this replaces (256x256, 256x192 or
-// 128x128 tiles by area and rounds).  Small tiles pay more per flop (each
+// a pair, which is never less; {} where a tile is not offered.
+//
+// Fitted to 5850 unsplit products (50 to 8224 rows, widths 192 to 24576), every
+// tile timed on each, with the operands in the 256 MB cache and with weights
+// and outputs rotated past it, weighted towards the tiles near each product's
+// best one: it is the picks that count.  Predicted times are 9-11% off on
+// average over all tiles.  The picks take 0.1-0.2% longer in total than each
+// product's best tile (weight gradients 0.5%).  Against the tiles that area and
+// rounds chose on the kernels before these they take 14 to 45% less, and no
+// forward or input-gradient pick is more than 1.1% slower (weight gradients: 8
+// of 1650 by more than 3%, at most 6.3%).  Small tiles pay more per flop (each
 // loads (bm + bn) / (bm * bn) operand bytes per flop into LDS, and a short
 // k-step is bound by its barrier and LDS latency) but fill the 256 CUs.
-// Products with a GELU or GELU' epilogue have rows of their own: the epilogue
-// of a 256x256 tile takes 21 and 24 us there against 10 and 7, and tiles two
-// to a CU hide it behind each other's loops (ViT-Base MLP-up forward 46 us on
-// 128x128 tiles against 59 on 256x192).
-enum GemmLayout { kFwd = 0, kDgrad = 1, kWgrad = 2, kFwdGelu = 3, kDgradGelu = 4 };
+//
+// Products with a GELU or GELU' epilogue have the same steps and a longer rest:
+// alone, the epilogue of a 256x256 tile takes 17 and 20 us there against 9 and
+// 6.  The forward GELU is not offered 192x128 tiles: timed by themselves they
+// are its best choice at times (1028 x 16384, K = 4096: 131 us against 151 on
+// 256x192), but in a layer, with the weights from HBM, they took 178 against 164.
+enum GemmLayout { kFwd = 0, kDgrad = 1, kWgrad = 2, kFwdGelu = 3, kDgradGelu = 4, kSplit = 5, kWgradSplit = 6 };
 
 struct TileShape {
   int bm, bn;
@@ -77,19 +84,19 @@ struct TileShape {
 
 struct TileCost {
   int bm, bn, per_cu;
-  float cost[5][4];  // [GemmLayout]: step, rest, step of a pair, rest of a pair
+  float cost[7][4];  // [GemmLayout]: step, rest, step of a pair, rest of a pair
 };
 
 constexpr TileCost kTiles[] = {
-    {256, 256, 1, {{0.94, 9.75}, {0.93, 7.29}, {1.24, 9.25}, {0.94, 20.98}, {0.93, 24.05}}},
-    {256, 192, 1, {{0.78, 9.38}, {0.83, 6.73}, {1.02, 8.98}, {0.78, 18.60}, {0.83, 19.00}}},
-    {128, 256, 1, {{0.60, 6.15}, {0.64, 4.66}, {0.61, 8.57}, {0.60, 12.24}, {0.64, 13.03}}},
-    {128, 192, 1, {{0.53, 5.89}, {0.55, 4.33}, {0.56, 5.71}, {0.53, 9.03}, {0.55, 9.02}}},
-    {192, 128, 2, {{0.72, 5.00, 0.97, 7.44}, {0.74, 4.50, 1.07, 2.36}, {0.75, 4.32, 1.13, 7.78}, {0.72, 9.50, 0.97, 20.00}, {0.74, 8.06, 1.07, 12.80}}},
-    {128, 128, 2, {{0.54, 7.89, 0.73, 5.68}, {0.59, 2.84, 0.74, 4.58}, {0.66, 0.77, 0.88, 4.44}, {0.54, 5.38, 0.73, 9.17}, {0.59, 4.71, 0.74, 9.63}}},
-    {64, 192, 1, {{0.39, 3.37}, {0.38, 2.90}, {0.40, 3.47}, {0.39, 5.62}, {0.38, 6.43}}},
-    {64, 128, 2, {{0.29, 2.50, 0.54, 2.18}, {0.28, 1.92, 0.53, 1.72}, {0.30, 2.66, 0.55, 2.21}, {0.29, 5.90, 0.54, 3.62}, {0.28, 7.95, 0.53, 3.77}}},
-    {64, 64, 2, {{0.17, 3.20, 0.36, 0.94}, {0.20, 0.86, 0.37, 0.77}, {0.25, 0.24, 0.39, 0.42}, {0.12, 2.94, 0.36, 1.46}, {0.20, 2.00, 0.37, 2.40}}}};
+    {256, 256, 1, {{1.20, 9.39}, {1.26, 6.30}, {1.38, 12.56}, {1.20, 16.96}, {1.26, 20.43}, {}, {1.11, 8.96}}},
+    {256, 192, 1, {{1.03, 9.40}, {1.06, 5.94}, {1.19, 7.90}, {1.03, 13.74}, {1.06, 13.64}, {}, {0.93, 8.59}}},
+    {128, 256, 1, {{0.72, 5.89}, {0.75, 4.48}, {0.76, 6.64}, {0.72, 8.84}, {0.75, 10.19}, {}, {0.60, 6.00}}},
+    {128, 192, 1, {{0.59, 5.51}, {0.61, 4.11}, {0.61, 5.05}, {0.59, 6.53}, {0.61, 7.78}, {}, {0.49, 5.42}}},
+    {192, 128, 2, {{0.75, 5.08, 1.14, 8.27}, {0.70, 3.66, 1.16, 4.36}, {0.78, 4.79, 1.21, 7.49}, {}, {0.70, 7.24, 1.16, 10.45}, {}, {0.68, 4.73, 1.10, 4.80}}},
+    {128, 128, 2, {{0.63, 4.05, 0.85, 6.47}, {0.63, 3.08, 0.82, 3.45}, {0.64, 4.25, 0.88, 4.71}, {0.63, 5.04, 0.85, 6.76}, {0.63, 5.47, 0.82, 7.93}, {0.59, 3.34, 0.78, 4.53}, {0.53, 3.43, 0.77, 3.43}}},
+    {64, 192, 1, {{0.46, 4.79}, {0.40, 3.55}, {0.42, 4.30}, {0.46, 5.42}, {0.40, 5.45}, {0.32, 3.46}, {}}},
+    {64, 128, 2, {{0.30, 3.78, 0.62, 3.96}, {0.29, 3.23, 0.55, 3.23}, {0.30, 3.55, 0.53, 3.78}, {0.30, 4.09, 0.62, 4.62}, {0.29, 4.51, 0.55, 4.55}, {0.26, 3.42, 0.51, 3.46}, {}}},
+    {64, 64, 2, {{0.20, 3.46, 0.33, 3.56}, {0.20, 3.14, 0.35, 3.14}, {0.27, 3.08, 0.36, 3.11}, {0.20, 3.66, 0.33, 3.70}, {0.20, 3.79, 0.35, 3.79}, {0.17, 3.27, 0.31, 3.27}, {}}}};
 
 // Predicted time (us) of `wgs` workgroups of a tile with nk k-steps each, in
 // rounds of per_cu workgroups on every CU.
@@ -114,8 +121,12 @@ inline TilePick pick_tile(int M, int N, int K, GemmLayout l) {
   TilePick best{{0, 0}, 0.f};
   for (const TileCost &t : kTiles) {
     // weight gradients over a few k-steps are their fp32 stores: 64-row tiles
-    // (whose loop is cheap, not their epilogue) only beyond five of them
-    if (l == kWgrad && t.bm < 128 && K <= 5 * 64) continue;
+    // (whose loop is cheap, not their epilogue) only beyond five of them, and
+    // tiles alone on their CU only beyond ten, as two to a CU overlap one's
+    // stores with the other's loop over several rounds (306 tokens, 4480 x
+    // 23488: 109 us on 128x128 tiles, 129 on 256x256, 122 before these kernels)
+    if (l == kWgrad && ((t.bm < 128 && K <= 5 * 64) || (t.per_cu == 1 && K <= 10 * 64))) continue;
+    if (t.cost[l][0] == 0.f) continue;  // not offered
     const float us = gemm_cost(t, l, tile_count(t, M, N), (K + 63) / 64);
     if (best.tile.bm == 0 || us < best.us) best = {{t.bm, t.bn}, us};
   }
@@ -129,12 +140,18 @@ inline TileShape choose_tile(int M, int N, int K, GemmLayout l) { return pick_ti
 // kernel adds them in split order (deterministic).  Weight gradients of at
 // most 64 tiles of 256x256, and forward and input-gradient products of at most
 // 32, split when their contraction holds two splits of kMinSplitTokens; which
-// products split is part of what callers size their workspaces by.  Tile and
-// number of splits minimise the cost model's time plus the second kernel's (5
-// us and its traffic at 4.5 TB/s, as measured on outputs of 0.3 to 2.4 M
-// values); every split covers at least kMinSplitTokens in whole 64-wide
-// k-steps (the last takes the remainder).  Tiles below 128x128 are worth it
-// only for forward and input-gradient products, where they fill the CUs.
+// products split is part of what callers size their workspaces by, and is not
+// weighed against the unsplit product.  Tile and number of splits minimise the
+// cost model's time plus the traffic of the second kernel (at 4.5 TB/s; its
+// launch is the same for all).  The splits' rows of the cost table are fitted
+// to 1620 products, every tile and split timed, forward and input gradients in
+// one row as they share a plan: predicted times are 9% off on average (weight
+// gradients 6%), and the picks are no slower than 128x128 splits were on the
+// kernels before these (1080 forward and input-gradient products: two by more
+// than 3%, at most 15%; 540 weight gradients: at most 2%).  Splits are whole 64-wide k-steps of equal length,
+// rounded up, of kMinSplitTokens on average or more: the last takes what
+// remains, which can be little.  Tiles below 128x128 are worth it only for
+// forward and input-gradient products, where they fill the CUs.
 constexpr int kMinSplitTokens = 512, kMaxSplits = 16;
 
 struct SplitPlan {
@@ -158,15 +175,16 @@ inline SplitPlan best_split(int M, int N, int K, GemmLayout l) {
   float best_us = 0.f;
   const int max_s = std::min(K / kMinSplitTokens, kMaxSplits);
   const int max_chunk = l == kWgrad ? wgrad_max_chunk(M, N, K) : K;
+  const GemmLayout row = l == kWgrad ? kWgradSplit : kSplit;
   for (const TileCost &t : kTiles) {
+    if (t.cost[row][0] == 0.f) continue;  // not offered
     const bool small = t.bm * t.bn < 128 * 128;
-    if (l == kWgrad ? t.bm < 128 : !small && (t.bm != 128 || t.bn != 128)) continue;
     const long n = tile_count(t, M, N);
     for (int s = 2; s <= max_s && (s == 2 || n * s <= 1024); ++s) {
-      if (l != kWgrad && small && n * s <= 256) continue;
+      if (small && n * s <= 256) continue;
       const int kc = ((K + s - 1) / s + 63) / 64 * 64;
       if ((K + kc - 1) / kc != s || kc > max_chunk) continue;
-      const float us = gemm_cost(t, l, n * s, kc / 64) +
+      const float us = gemm_cost(t, row, n * s, kc / 64) +
                        static_cast<float>(s + 1) * static_cast<float>(M) * static_cast<float>(N) * (4.f / 4.5e6f);
       if (best.splits == 1 || us < best_us) {
         best_us = us;
