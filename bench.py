@@ -105,7 +105,8 @@ def _tile_of(pid, nb, tiles_m, tiles_n, gm=4):
     """Output tile of workgroup pid in an unsplit GEMM grid of nb workgroups,
     in the kernels' order (workgroup i runs on XCD i % 8): with an even grid
     of at least 2 * gm row tiles, two M-halves of four XCDs each, every XCD
-    walking its block in groups of gm row tiles (4 for 256-row tiles, else 8);
+    walking its block in groups of gm row tiles (8 for the direct-to-LDS
+    kernels' tiles below 256 rows, else 4);
     otherwise one contiguous range of tiles per XCD, in groups of 8 row
     tiles."""
     xcd, local = pid & 7, pid >> 3
@@ -131,13 +132,15 @@ def _split_item(pid, nb, tiles_m, tiles_n):
     return split, t % tiles_m, t // tiles_m
 
 
-def fetch_floor(rows, cols, K, bm, bn, splits):
+def fetch_floor(rows, cols, K, bm, bn, splits, staged=False):
     """Operand bytes the eight L2s must fetch at least for one GEMM launch
     (output rows x cols, contraction K, bf16 operands): the workgroups of a
     round run together (one per CU, two for the tiles that share one), the eighth of
     them on one XCD share its L2, and an operand panel (a tile row's or tile
     column's slice of the contraction) outlives neither its round nor its
-    XCD.  Each round's distinct panels per XCD, summed."""
+    XCD.  Each round's distinct panels per XCD, summed.  staged: the
+    register-staged kernel runs the product (another tile order)."""
+    gm = 4 if bm == 256 or staged else 8
     per_round = 512 if (bm, bn) in ((192, 128), (128, 128), (64, 128), (64, 64)) else 256
     tm, tn = -(-rows // bm), -(-cols // bn)
     nb = tm * tn * splits
@@ -148,7 +151,7 @@ def fetch_floor(rows, cols, K, bm, bn, splits):
     for r0 in range(0, nb, per_round):
         panels = {}
         for pid in range(r0, min(nb, r0 + per_round)):
-            sp, a, b = _split_item(pid, nb, tm, tn) if splits > 1 else (0, *_tile_of(pid, nb, tm, tn, 4 if bm == 256 else 8))
+            sp, a, b = _split_item(pid, nb, tm, tn) if splits > 1 else (0, *_tile_of(pid, nb, tm, tn, gm))
             klen = min(K - sp * kc, kc)
             rs, cs = panels.setdefault(pid & 7, (set(), set()))
             rs.add((a, sp, min(bm, rows - a * bm) * klen))
@@ -166,9 +169,11 @@ def gemm_fetch_floors(cfg):
             bm, bn, sp = B.linear_plan(B.LAYOUT_WGRAD, m, nn, k)
             out[n] = fetch_floor(nn, k, m, bm, bn, sp)
         else:
-            layout = B.LAYOUT_DGRAD if n.endswith("_bwd_data") else B.LAYOUT_FWD
+            layout = {"mlp_up_fwd": B.LAYOUT_FWD_GELU, "mlp_down_bwd_data": B.LAYOUT_DGRAD_GELU}.get(
+                n, B.LAYOUT_DGRAD if n.endswith("_bwd_data") else B.LAYOUT_FWD)
             bm, bn, sp = B.linear_plan(layout, m, nn, k)
-            out[n] = fetch_floor(m, nn, k, bm, bn, sp)
+            # contiguous contractions that are no multiple of 64 are staged
+            out[n] = fetch_floor(m, nn, k, bm, bn, sp, staged=k % 64 != 0)
     return out
 
 

@@ -559,17 +559,25 @@ int enc_calib_copy(const void *src, void *dst, size_t bytes, enc_stream_t stream
  * traffic or dispatches: the output tile (*tile_rows x *tile_cols of the
  * output as stored) and the number of contraction splits (*splits, 1 when
  * not split) that the entry points use when given a workspace of the size
- * their query returns (with ws = NULL nothing is split).  The products with a
- * GELU or GELU' epilogue (enc_mlp_up_fwd, enc_mlp_down_bwd_data) may run
- * another tile, as their epilogue is longer; their splits are the same.  layout:
+ * their query returns (with ws = NULL nothing is split).  layout:
  *   ENC_LAYOUT_FWD    the forward projections: output [M, N] = X[M, K] W^T
  *   ENC_LAYOUT_DGRAD  the input gradients: output [M, N] = dY[M, K] W[K, N]
  *   ENC_LAYOUT_WGRAD  the weight gradients: dW[N, K] over M tokens (M, N, K
  *                     as enc_linear_bwd_weight)
+ *   ENC_LAYOUT_FWD_GELU, ENC_LAYOUT_DGRAD_GELU  the same for the two products
+ *                     with a longer epilogue, enc_mlp_up_fwd (GELU) and
+ *                     enc_mlp_down_bwd_data (GELU'), which choose tiles of
+ *                     their own
  * Sizes follow the entry points' rules (ENC_ERR_INVALID / ENC_ERR_UNSUPPORTED
  * as they would return); ENC_ERR_INVALID for another layout or a NULL
  * output.  Host only: touches no device. */
-enum { ENC_LAYOUT_FWD = 0, ENC_LAYOUT_DGRAD = 1, ENC_LAYOUT_WGRAD = 2 };
+enum {
+  ENC_LAYOUT_FWD = 0,
+  ENC_LAYOUT_DGRAD = 1,
+  ENC_LAYOUT_WGRAD = 2,
+  ENC_LAYOUT_FWD_GELU = 3,
+  ENC_LAYOUT_DGRAD_GELU = 4
+};
 int enc_linear_plan(int layout, int M, int N, int K, int *tile_rows, int *tile_cols, int *splits);
 
 #ifdef __cplusplus

@@ -420,7 +420,7 @@ def linear_workspace_bytes(M, N, K):
     return n.value
 
 
-LAYOUT_FWD, LAYOUT_DGRAD, LAYOUT_WGRAD = 0, 1, 2
+LAYOUT_FWD, LAYOUT_DGRAD, LAYOUT_WGRAD, LAYOUT_FWD_GELU, LAYOUT_DGRAD_GELU = 0, 1, 2, 3, 4
 
 
 def linear_plan(layout, M, N, K):

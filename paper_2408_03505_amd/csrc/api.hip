@@ -689,7 +689,8 @@ int enc_linear_bwd_weight_workspace_bytes(int M, int N, int K, size_t *bytes) {
 
 int enc_linear_plan(int layout, int M, int N, int K, int *tile_rows, int *tile_cols, int *splits) {
   const char *fn = "enc_linear_plan";
-  if (layout != ENC_LAYOUT_FWD && layout != ENC_LAYOUT_DGRAD && layout != ENC_LAYOUT_WGRAD)
+  const bool gelu = layout == ENC_LAYOUT_FWD_GELU || layout == ENC_LAYOUT_DGRAD_GELU;
+  if (layout != ENC_LAYOUT_FWD && layout != ENC_LAYOUT_DGRAD && layout != ENC_LAYOUT_WGRAD && !gelu)
     return fail(ENC_ERR_INVALID, "%s: unknown layout %d", fn, layout);
   int r = linear_dims(fn, M, {N, K});
   if (r) return r;
@@ -699,16 +700,16 @@ int enc_linear_plan(int layout, int M, int N, int K, int *tile_rows, int *tile_c
   // the GemmArgs geometry the launch helpers above build for each layout
   GemmArgs a{};
   bool AT = false, BT = false;
-  if (layout == ENC_LAYOUT_FWD) {
+  if (layout == ENC_LAYOUT_FWD || layout == ENC_LAYOUT_FWD_GELU) {
     a.M = M, a.N = N, a.K = K, a.lda = K, a.ldb = K;
-  } else if (layout == ENC_LAYOUT_DGRAD) {
+  } else if (layout == ENC_LAYOUT_DGRAD || layout == ENC_LAYOUT_DGRAD_GELU) {
     a.M = M, a.N = N, a.K = K, a.lda = K, a.ldb = N;
     BT = true;
   } else {
     a.M = N, a.N = K, a.K = M, a.lda = N, a.ldb = K;
     AT = BT = true;
   }
-  const GemmPlan pl = gemm_plan(a.M, a.N, a.K, a.lda, a.ldb, AT, BT);
+  const GemmPlan pl = gemm_plan(a.M, a.N, a.K, a.lda, a.ldb, AT, BT, gelu);
   *tile_rows = pl.tile.bm;
   *tile_cols = pl.tile.bn;
   *splits = pl.splits;

@@ -1287,12 +1287,8 @@ bool launch_lds(const GemmArgs &a, hipStream_t s, TileShape t) {
 
 template <bool AT, bool BT, Epi EPI>
 bool launch_lds(const GemmArgs &a, hipStream_t s) {
-  constexpr GemmLayout kind = AT                      ? kWgrad
-                              : EPI == Epi::kBiasGelu ? kFwdGelu
-                              : EPI == Epi::kGeluGrad ? kDgradGelu
-                              : BT                    ? kDgrad
-                                                      : kFwd;
-  return launch_lds<AT, BT, EPI>(a, s, choose_tile(a.M, a.N, a.K, kind));
+  constexpr bool gelu = EPI == Epi::kBiasGelu || EPI == Epi::kGeluGrad;
+  return launch_lds<AT, BT, EPI>(a, s, choose_tile(a.M, a.N, a.K, gemm_layout(AT, BT, gelu)));
 }
 
 }  // namespace

@@ -65,7 +65,7 @@ inline size_t attn_bwd_ws_bytes(int B, int S, int heads) {
 // best one: it is the picks that count.  Predicted times are 9-11% off on
 // average over all tiles.  The picks take 0.1-0.2% longer in total than each
 // product's best tile (weight gradients 0.5%).  Against the tiles that area and
-// rounds chose on the kernels before these they take 14 to 45% less, and no
+// rounds chose on the kernels before these they take 31 to 45% less, and no
 // forward or input-gradient pick is more than 1.1% slower (weight gradients: 8
 // of 1650 by more than 3%, at most 6.3%).  Small tiles pay more per flop (each
 // loads (bm + bn) / (bm * bn) operand bytes per flop into LDS, and a short
@@ -77,6 +77,12 @@ inline size_t attn_bwd_ws_bytes(int B, int S, int heads) {
 // are its best choice at times (1028 x 16384, K = 4096: 131 us against 151 on
 // 256x192), but in a layer, with the weights from HBM, they took 178 against 164.
 enum GemmLayout { kFwd = 0, kDgrad = 1, kWgrad = 2, kFwdGelu = 3, kDgradGelu = 4, kSplit = 5, kWgradSplit = 6 };
+
+// Row of the cost table of an unsplit product with operands A, B (AT, BT:
+// stored k-major) and, with `gelu`, a GELU or GELU' epilogue.
+constexpr GemmLayout gemm_layout(bool AT, bool BT, bool gelu) {
+  return AT ? kWgrad : BT ? (gelu ? kDgradGelu : kDgrad) : (gelu ? kFwdGelu : kFwd);
+}
 
 struct TileShape {
   int bm, bn;
@@ -240,19 +246,19 @@ inline TileShape any_tile(int M, int N) {
 // Output tile and contraction splits of a product as the launchers take it
 // when given a workspace of the queried size (forward: AT = BT = false;
 // input gradient: BT; weight gradient: AT and BT, M output rows, N output
-// columns, K tokens).
+// columns, K tokens; gelu: with a GELU or GELU' epilogue).
 struct GemmPlan {
   TileShape tile;
   int splits;
 };
 
-inline GemmPlan gemm_plan(int M, int N, int K, int lda, int ldb, bool AT, bool BT) {
+inline GemmPlan gemm_plan(int M, int N, int K, int lda, int ldb, bool AT, bool BT, bool gelu) {
   const bool wgrad = AT && BT;
   const bool fits = lds_fits(M, N, K, lda, ldb, AT, BT);
   const SplitPlan sp = wgrad ? wgrad_split_plan(M, N, K) : gemm_split_plan(M, N, K);
   const bool split_ok = wgrad ? M % 4 == 0 && N % 4 == 0 : N % 8 == 0;
   if (sp.splits > 1 && split_ok && fits) return {sp.tile, sp.splits};
-  if (fits) return {choose_tile(M, N, K, wgrad ? kWgrad : BT ? kDgrad : kFwd), 1};
+  if (fits) return {choose_tile(M, N, K, gemm_layout(AT, BT, gelu)), 1};
   return {any_tile(M, N), 1};
 }
 

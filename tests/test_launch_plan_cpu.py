@@ -60,3 +60,46 @@ def test_weight_gradients_over_ten_steps_or_less_run_two_workgroups_to_a_cu():
     for _ in range(2000):
         M, N, K = rng.randint(1, 640), 8 * rng.randint(1, 1024), 8 * rng.randint(1, 1024)
         assert B.linear_plan(B.LAYOUT_WGRAD, M, N, K)[:2] in {(192, 128), (128, 128), (64, 128), (64, 64)}, (M, N, K)
+
+
+def test_gelu_products_have_plans_of_their_own():
+    # ViT-Base: 256x192 tiles for the plain MLP-up product, 128x128 with the
+    # GELU epilogue; splits and the register-staged kernel's tiles are shared
+    assert B.linear_plan(B.LAYOUT_FWD, 6304, 3072, 768) == (256, 192, 1)
+    assert B.linear_plan(B.LAYOUT_FWD_GELU, 6304, 3072, 768) == (128, 128, 1)
+    pairs = ((B.LAYOUT_FWD, B.LAYOUT_FWD_GELU), (B.LAYOUT_DGRAD, B.LAYOUT_DGRAD_GELU))
+    rng = random.Random(8)
+    differ = 0
+    for _ in range(1000):
+        M, N, K = rng.randint(1, 8224), 8 * rng.randint(1, 1024), rng.choice((8, 64)) * rng.randint(1, 96)
+        for plain, gelu in pairs:
+            a, b = B.linear_plan(plain, M, N, K), B.linear_plan(gelu, M, N, K)
+            assert a[2] == b[2] and (a == b or (a[2] == 1 and K % 64 == 0)), (M, N, K)
+            differ += a != b
+    assert differ > 50
+    for layout in (-1, 5):
+        with pytest.raises(B.EncError):
+            B.linear_plan(layout, 64, 64, 64)
+
+
+def test_fetch_floors_are_those_of_the_tiles_that_run():
+    import bench
+    from paper_2408_03505_amd.synthetic import CONFIGS
+    cfg = CONFIGS["vit_base"]
+    floors = bench.gemm_fetch_floors(cfg)
+    M, H, F = cfg["batch"] * cfg["seq"], cfg["hidden"], cfg["mlp"]
+    for n, layout in (("mlp_up_fwd", B.LAYOUT_FWD_GELU), ("mlp_down_bwd_data", B.LAYOUT_DGRAD_GELU)):
+        assert floors[n] == bench.fetch_floor(M, F, H, *B.linear_plan(layout, M, F, H)), n
+    # a contraction that is no multiple of 64: the register-staged kernel walks
+    # its 128x128 tiles in groups of 4 rows, not 8
+    odd = dict(cfg, hidden=776, seq=256, batch=16)
+    assert bench.gemm_fetch_floors(odd)["mlp_up_fwd"] == bench.fetch_floor(4096, F, 776, 128, 128, 1, staged=True)
+    assert bench.fetch_floor(4096, F, 776, 128, 128, 1, staged=True) != bench.fetch_floor(4096, F, 776, 128, 128, 1)
+
+
+@pytest.mark.parametrize("gm", (4, 8))
+@pytest.mark.parametrize("tm,tn", [(8, 96), (16, 72), (32, 24), (24, 32), (18, 4), (9, 5), (1, 1)])
+def test_tile_orders_cover_every_tile_once(tm, tn, gm):
+    import bench
+    nb = tm * tn
+    assert sorted(bench._tile_of(p, nb, tm, tn, gm) for p in range(nb)) == [(a, b) for a in range(tm) for b in range(tn)]
