@@ -123,6 +123,13 @@ struct TilePick {
   float us;
 };
 
+// Whether a tile may run an output [M, N].  The 256-row kernels load a tile in
+// halves, the second one up to 64 rows (columns) of the operand further by a
+// scalar offset.  The buffer's range check takes that offset off the operand's
+// size, so it must not be larger: more than 64 rows and columns.  (No product
+// of that kind is fastest on a 256-row tile.)
+inline bool tile_allowed(const TileCost &t, int M, int N) { return t.bm < 256 || (M > 64 && N > 64); }
+
 inline TilePick pick_tile(int M, int N, int K, GemmLayout l) {
   TilePick best{{0, 0}, 0.f};
   for (const TileCost &t : kTiles) {
@@ -132,7 +139,7 @@ inline TilePick pick_tile(int M, int N, int K, GemmLayout l) {
     // stores with the other's loop over several rounds (306 tokens, 4480 x
     // 23488: 109 us on 128x128 tiles, 129 on 256x256, 122 before these kernels)
     if (l == kWgrad && ((t.bm < 128 && K <= 5 * 64) || (t.per_cu == 1 && K <= 10 * 64))) continue;
-    if (t.cost[l][0] == 0.f) continue;  // not offered
+    if (t.cost[l][0] == 0.f || !tile_allowed(t, M, N)) continue;
     const float us = gemm_cost(t, l, tile_count(t, M, N), (K + 63) / 64);
     if (best.tile.bm == 0 || us < best.us) best = {{t.bm, t.bn}, us};
   }
@@ -183,7 +190,7 @@ inline SplitPlan best_split(int M, int N, int K, GemmLayout l) {
   const int max_chunk = l == kWgrad ? wgrad_max_chunk(M, N, K) : K;
   const GemmLayout row = l == kWgrad ? kWgradSplit : kSplit;
   for (const TileCost &t : kTiles) {
-    if (t.cost[row][0] == 0.f) continue;  // not offered
+    if (t.cost[row][0] == 0.f || !tile_allowed(t, M, N)) continue;
     const bool small = t.bm * t.bn < 128 * 128;
     const long n = tile_count(t, M, N);
     for (int s = 2; s <= max_s && (s == 2 || n * s <= 1024); ++s) {

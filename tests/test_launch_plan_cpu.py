@@ -103,3 +103,18 @@ def test_tile_orders_cover_every_tile_once(tm, tn, gm):
     import bench
     nb = tm * tn
     assert sorted(bench._tile_of(p, nb, tm, tn, gm) for p in range(nb)) == [(a, b) for a in range(tm) for b in range(tn)]
+
+
+def test_narrow_products_never_run_256_row_tiles():
+    # the 256-row kernels' second half tiles start up to 64 rows into an operand
+    for layout in range(5):
+        for narrow in (8, 24, 40, 56, 64):
+            for wide in (8, 256, 4096, 49152, 65536, 131072):
+                for k in (64, 1024, 8192, 16320):
+                    if wide * k >= 2 ** 31:
+                        continue
+                    for rows, cols in ((narrow, wide), (wide, narrow)):
+                        # a weight gradient's output is [N, K] over M tokens
+                        args = (k, rows, cols) if layout == B.LAYOUT_WGRAD else (rows, cols, k)
+                        bm, bn, _ = B.linear_plan(layout, *args)
+                        assert bm < 256 or (bm, bn) == (256, 128), (layout, rows, cols, k)
