@@ -160,26 +160,20 @@ struct BwdWs {
   size_t total;
 };
 
-// Partial sums of the layer's split input gradients and forward projections
-// (each GEMM uses the region in turn): the largest need of the four of each.
-size_t layer_dgrad_fwd_ws(const enc_cfg_t *c) {
+// Partial sums of the layer's split input gradients and of its split forward
+// projections (each GEMM uses the region in turn): the largest need of the four.
+size_t layer_dgrad_ws(const enc_cfg_t *c) {
   const int M = c->batch * c->seq, H = c->hidden, A = c->heads * c->head_dim, F = c->mlp;
-  // input gradients: du [M, F] over H, dy2 [M, H] over F, dO [M, A] over H, dy1 [M, H] over 3A
-  const size_t dg = std::max(std::max(gemm_ws_bytes(M, F, H), gemm_ws_bytes(M, H, F)),
-                             std::max(gemm_ws_bytes(M, A, H), gemm_ws_bytes(M, H, 3 * A)));
-  // forward: qkv [M, 3A] over H, h [M, H] over A, u [M, F] over H, out [M, H] over F
-  const size_t fw = std::max(std::max(gemm_ws_bytes(M, 3 * A, H), gemm_ws_bytes(M, H, A)),
-                             std::max(gemm_ws_bytes(M, F, H), gemm_ws_bytes(M, H, F)));
-  return std::max(dg, fw);
+  // du [M, F] over H, dy2 [M, H] over F, dO [M, A] over H, dy1 [M, H] over 3A
+  return std::max(std::max(gemm_ws_bytes(M, F, H), gemm_ws_bytes(M, H, F)),
+                  std::max(gemm_ws_bytes(M, A, H), gemm_ws_bytes(M, H, 3 * A)));
 }
 
-// What the forward composite asks of a given workspace: the largest need of
-// any of the layer's split products.
-size_t layer_gemm_ws(const enc_cfg_t *c) {
+size_t layer_fwd_ws(const enc_cfg_t *c) {
   const int M = c->batch * c->seq, H = c->hidden, A = c->heads * c->head_dim, F = c->mlp;
-  const size_t wg = std::max(std::max(gemm_wgrad_ws_bytes(H, F, M), gemm_wgrad_ws_bytes(F, H, M)),
-                             std::max(gemm_wgrad_ws_bytes(H, A, M), gemm_wgrad_ws_bytes(3 * A, H, M)));
-  return std::max(wg, layer_dgrad_fwd_ws(c));
+  // qkv [M, 3A] over H, h [M, H] over A, u [M, F] over H, out [M, H] over F
+  return std::max(std::max(gemm_ws_bytes(M, 3 * A, H), gemm_ws_bytes(M, H, A)),
+                  std::max(gemm_ws_bytes(M, F, H), gemm_ws_bytes(M, H, F)));
 }
 
 BwdWs bwd_layout(const enc_cfg_t *c) {
@@ -206,7 +200,7 @@ BwdWs bwd_layout(const enc_cfg_t *c) {
   w.wg_bytes[2] = gemm_wgrad_ws_bytes(iH, iA, iM);
   w.wg_bytes[3] = gemm_wgrad_ws_bytes(3 * iA, iH, iM);
   for (int i = 0; i < 4; ++i) w.wg[i] = take(w.wg_bytes[i]);
-  w.dg_bytes = layer_dgrad_fwd_ws(c);
+  w.dg_bytes = layer_dgrad_ws(c);
   w.dg = take(w.dg_bytes);
   w.total = off;
   return w;
@@ -491,7 +485,7 @@ int enc_layer_workspace_bytes(const enc_cfg_t *cfg, size_t *bytes) {
   int r = check_cfg("enc_layer_workspace_bytes", cfg);
   if (r) return r;
   if (!bytes) return fail(ENC_ERR_INVALID, "enc_layer_workspace_bytes: bytes is NULL");
-  *bytes = bwd_layout(cfg).total;
+  *bytes = std::max(bwd_layout(cfg).total, layer_fwd_ws(cfg));
   return ok();
 }
 
@@ -821,7 +815,7 @@ int encoder_layer_fwd(const enc_cfg_t *cfg, const enc_params_t *params, const en
   c.req(x, "x").req(out, "out").req(saved, "saved").opt(ws, "ws");
   if (c.code) return c.code;
   // the workspace only holds split-product partials here (ws = NULL: no split)
-  const size_t gneed = layer_gemm_ws(cfg);
+  const size_t gneed = layer_fwd_ws(cfg);
   if (ws && ws_bytes < gneed) return fail(ENC_ERR_WORKSPACE, "%s: workspace %zu bytes < %zu needed", fn, ws_bytes, gneed);
   void *gp = ws && gneed ? ws : nullptr;
   enc_saved_layout_t L;

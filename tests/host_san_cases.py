@@ -148,3 +148,19 @@ def test_layer_backward_defers_its_sums_only_into_distinct_outputs():
             assert deferred(ptrs[:i] + [ptrs[i] + 16] + ptrs[i + 1:]) == 0, i
         if i > 0:
             assert deferred(ptrs[:i] + [ptrs[i] - 16] + ptrs[i + 1:]) == 0, i
+
+
+@pytest.mark.parametrize("cfg", CFGS + [dict(batch=2, seq=257, hidden=1280, heads=16, head_dim=80, mlp=5120, ln_eps=1e-6)])
+def test_layer_forward_asks_for_its_own_products_workspace_only(cfg):
+    c = B.make_cfg(cfg)
+    params = B.EncParams(*[0x10000] * 12)
+    M, H, A, F = cfg["batch"] * cfg["seq"], cfg["hidden"], cfg["heads"] * cfg["head_dim"], cfg["mlp"]
+    need = max(B.linear_workspace_bytes(M, n, k) for n, k in ((3 * A, H), (H, A), (F, H), (H, F)))
+    assert need <= B.layer_workspace_bytes(cfg)
+
+    def fwd(nbytes):
+        return L.encoder_layer_fwd(ctypes.byref(c), ctypes.byref(params), P, P, P, P, nbytes, S0)
+
+    assert fwd(need) == B.ENC_OK
+    if need:
+        assert fwd(need - 1) == B.ENC_ERR_WORKSPACE
