@@ -996,21 +996,18 @@ bool launch_half_cfg(const GemmArgs &a, uint32_t a_bytes, uint32_t b_bytes, hipS
 template <int ROWS, int F, int S, bool TRANS>
 struct RingTile {
   static constexpr int BK = 64, KS = 2;
-  static constexpr int LROWS = TRANS ? (ROWS + 63) / 64 * 64 : ROWS;  // (transposed rows padded to 128 bytes)
-  static constexpr int BYTES = LROWS * BK * 2, WB = BYTES / 8, NI = (WB + 1023) / 1024;
-  static constexpr bool MASKED = ROWS != LROWS || WB % 1024 != 0;
+  static constexpr int BYTES = ROWS * BK * 2, WB = BYTES / 8, NI = WB / 1024;  // per wave: whole 1 KB loads
   static constexpr int G = 65536 / BYTES < S ? 65536 / BYTES : S;  // stages one address register reaches
   static constexpr int NG = (S + G - 1) / G, NOFF = TRANS ? F : KS;
-  static_assert(WB % 16 == 0 && ROWS % 16 == 0 && G >= 1, "tile shape");
+  static_assert(ROWS % 64 == 0 && G >= 1, "tile shape");
   uint32_t voff[NI];
-  uint64_t mask[NI];
   u32x4_t rsrc;
   int off[NG][NOFF];
 
   // 128-byte multiples alternate between the halves of a 256-byte bank line
   // from k-row to k-row, so one XOR bit less spreads the eight k-rows
   __device__ static __forceinline__ int swz(int k) {
-    return LROWS % 128 == 0 ? t_swz(k) : ((((k >> 1) & 1) | (((k >> 3) & 1) << 1)) << 1);
+    return ROWS % 128 == 0 ? t_swz(k) : ((((k >> 1) & 1) | (((k >> 3) & 1) << 1)) << 1);
   }
   __device__ __forceinline__ void init(const bf16_t *base, uint32_t nbytes, int ld, int r0, int w, int wid, int lane,
                                        int lds_base) {
@@ -1018,19 +1015,16 @@ struct RingTile {
 #pragma unroll
     for (int i = 0; i < NI; ++i) {
       const int o = wid * WB + i * 1024 + lane * 16;
-      bool live = i * 1024 + lane * 16 < WB;
       if constexpr (!TRANS) {
         using T = NtTile<BK>;
         const int r = o / T::RB, pch = (o % T::RB) >> 4;
         const int c = pch ^ ((r / T::RP) % T::CPR);
         voff[i] = static_cast<uint32_t>(((r0 + r) * static_cast<long>(ld) + c * 8) * 2);
       } else {
-        const int k = o / (LROWS * 2), pch = (o % (LROWS * 2)) >> 4;
+        const int k = o / (ROWS * 2), pch = (o % (ROWS * 2)) >> 4;
         const int c = (pch ^ swz(k)) * 8;
-        live = live && c < ROWS;
         voff[i] = static_cast<uint32_t>((k * static_cast<long>(ld) + r0 + c) * 2);
       }
-      mask[i] = __ballot(live);
     }
 #pragma unroll
     for (int g = 0; g < NG; ++g) {
@@ -1044,7 +1038,7 @@ struct RingTile {
 #pragma unroll
         for (int f = 0; f < F; ++f) {
           const int n = w * F * 16 + f * 16 + 4 * (lane & 3);
-          off[g][f] = gb + k * (LROWS * 2) + (((n >> 3) ^ swz(k)) << 4) + (n & 7) * 2;
+          off[g][f] = gb + k * (ROWS * 2) + (((n >> 3) ^ swz(k)) << 4) + (n & 7) * 2;
         }
       }
 #pragma unroll
@@ -1054,10 +1048,7 @@ struct RingTile {
   template <int OFF, int I = 0>
   __device__ __forceinline__ void issue(uint32_t wbase, uint32_t soff) const {
     if constexpr (I < NI) {
-      if constexpr (MASKED)
-        issue_lds16<OFF + I * 1024>(rsrc, wbase, voff[I], soff, mask[I]);
-      else
-        issue_lds16<OFF + I * 1024>(rsrc, wbase, voff[I], soff);
+      issue_lds16<OFF + I * 1024>(rsrc, wbase, voff[I], soff);
       issue<OFF, I + 1>(wbase, soff);
     }
   }
@@ -1068,8 +1059,8 @@ struct RingTile {
       return *reinterpret_cast<const __attribute__((address_space(3))) bf16x8_t *>(q + off[ST / G][kk] +
                                                                                      f * 16 * BK * 2);
     } else {
-      q += off[ST / G][f] + kk * 32 * LROWS * 2;
-      return lds_read_tr(q, q + 4 * LROWS * 2);
+      q += off[ST / G][f] + kk * 32 * ROWS * 2;
+      return lds_read_tr(q, q + 4 * ROWS * 2);
     }
   }
 };
