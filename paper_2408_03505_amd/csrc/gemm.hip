@@ -1252,9 +1252,13 @@ bool launch_ring_cfg(const GemmArgs &a, uint32_t a_bytes, uint32_t b_bytes, hipS
 
 // Direct-to-LDS path on tile t (of kTiles): 256-row tiles run gemm_half_kernel,
 // the others gemm_ring_kernel.
-// Returns false when the operands do not fit the path's constraints.
+// Returns false when the operands do not fit the path's constraints.  Only the
+// tiles that the cost table offers these products are compiled (forward and
+// input-gradient products write fp32 as partials of a split only).
 template <bool AT, bool BT, Epi EPI>
 bool launch_lds(const GemmArgs &a, hipStream_t s, TileShape t) {
+  constexpr bool gelu = EPI == Epi::kBiasGelu || EPI == Epi::kGeluGrad;
+  constexpr GemmLayout row = !AT && EPI == Epi::kF32 ? kSplit : gemm_layout(AT, BT, gelu);
   if (!lds_fits(a.M, a.N, a.K, a.lda, a.ldb, AT, BT)) return false;
   // operand extents (bytes) bound the buffer loads
   const uint32_t ab = static_cast<uint32_t>(static_cast<uint64_t>(AT ? a.K : a.M) * a.lda * 2);
@@ -1265,15 +1269,25 @@ bool launch_lds(const GemmArgs &a, hipStream_t s, TileShape t) {
   // the ViT-Base QKV input gradient, 64x128 13.4 against 14.6 at a quarter of
   // its tokens.  64-row tiles with two strided operands are even or better
   // with them.
-  if (t.bm == 256 && t.bn == 256) return launch_half_cfg<2, 4, 4, 2, AT, BT, EPI>(a, ab, bb, s);
-  if (t.bm == 256) return launch_half_cfg<4, 2, 2, 3, AT, BT, EPI>(a, ab, bb, s);
-  if (t.bm == 128 && t.bn == 256) return launch_ring_cfg<2, 4, 4, 4, 3, 1, true, AT, BT, EPI>(a, ab, bb, s);
-  if (t.bm == 128 && t.bn == 192) return launch_ring_cfg<2, 4, 4, 3, 4, 1, true, AT, BT, EPI>(a, ab, bb, s);
-  if (t.bm == 192) return launch_ring_cfg<4, 2, 3, 4, 2, 2, false, AT, BT, EPI>(a, ab, bb, s);
-  if (t.bm == 128) return launch_ring_cfg<2, 4, 4, 2, 2, 2, false, AT, BT, EPI>(a, ab, bb, s);
-  if (t.bn == 192) return launch_ring_cfg<2, 4, 2, 3, 4, 1, AT, AT, BT, EPI>(a, ab, bb, s);
-  if (t.bn == 128) return launch_ring_cfg<2, 4, 2, 2, 3, 2, AT, AT, BT, EPI>(a, ab, bb, s);
-  return launch_ring_cfg<2, 4, 2, 1, 4, 2, false, AT, BT, EPI>(a, ab, bb, s);
+  if constexpr (tile_offered(256, 256, row))
+    if (t.bm == 256 && t.bn == 256) return launch_half_cfg<2, 4, 4, 2, AT, BT, EPI>(a, ab, bb, s);
+  if constexpr (tile_offered(256, 192, row))
+    if (t.bm == 256 && t.bn == 192) return launch_half_cfg<4, 2, 2, 3, AT, BT, EPI>(a, ab, bb, s);
+  if constexpr (tile_offered(128, 256, row))
+    if (t.bm == 128 && t.bn == 256) return launch_ring_cfg<2, 4, 4, 4, 3, 1, true, AT, BT, EPI>(a, ab, bb, s);
+  if constexpr (tile_offered(128, 192, row))
+    if (t.bm == 128 && t.bn == 192) return launch_ring_cfg<2, 4, 4, 3, 4, 1, true, AT, BT, EPI>(a, ab, bb, s);
+  if constexpr (tile_offered(192, 128, row))
+    if (t.bm == 192 && t.bn == 128) return launch_ring_cfg<4, 2, 3, 4, 2, 2, false, AT, BT, EPI>(a, ab, bb, s);
+  if constexpr (tile_offered(128, 128, row))
+    if (t.bm == 128 && t.bn == 128) return launch_ring_cfg<2, 4, 4, 2, 2, 2, false, AT, BT, EPI>(a, ab, bb, s);
+  if constexpr (tile_offered(64, 192, row))
+    if (t.bm == 64 && t.bn == 192) return launch_ring_cfg<2, 4, 2, 3, 4, 1, AT, AT, BT, EPI>(a, ab, bb, s);
+  if constexpr (tile_offered(64, 128, row))
+    if (t.bm == 64 && t.bn == 128) return launch_ring_cfg<2, 4, 2, 2, 3, 2, AT, AT, BT, EPI>(a, ab, bb, s);
+  if constexpr (tile_offered(64, 64, row))
+    if (t.bm == 64 && t.bn == 64) return launch_ring_cfg<2, 4, 2, 1, 4, 2, false, AT, BT, EPI>(a, ab, bb, s);
+  return false;
 }
 
 template <bool AT, bool BT, Epi EPI>

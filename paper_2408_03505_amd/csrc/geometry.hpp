@@ -104,6 +104,22 @@ constexpr TileCost kTiles[] = {
     {64, 128, 2, {{0.30, 3.78, 0.62, 3.96}, {0.29, 3.23, 0.55, 3.23}, {0.30, 3.55, 0.53, 3.78}, {0.30, 4.09, 0.62, 4.62}, {0.29, 4.51, 0.55, 4.55}, {0.26, 3.42, 0.51, 3.46}, {}}},
     {64, 64, 2, {{0.20, 3.46, 0.33, 3.56}, {0.20, 3.14, 0.35, 3.14}, {0.27, 3.08, 0.36, 3.11}, {0.20, 3.66, 0.33, 3.70}, {0.20, 3.79, 0.35, 3.79}, {0.17, 3.27, 0.31, 3.27}, {}}}};
 
+// Whether the table offers a tile to the products of a row.
+constexpr bool tile_offered(int bm, int bn, GemmLayout l) {
+  for (const TileCost &t : kTiles)
+    if (t.bm == bm && t.bn == bn) return t.cost[l][0] != 0.f;
+  return false;
+}
+
+// Every split tile of a weight gradient is one of its unsplit tiles too: the
+// same kernels run both.
+constexpr bool split_tiles_run_unsplit() {
+  for (const TileCost &t : kTiles)
+    if (t.cost[kWgradSplit][0] != 0.f && t.cost[kWgrad][0] == 0.f) return false;
+  return true;
+}
+static_assert(split_tiles_run_unsplit(), "weight-gradient tiles");
+
 // Predicted time (us) of `wgs` workgroups of a tile with nk k-steps each, in
 // rounds of per_cu workgroups on every CU.
 inline float gemm_cost(const TileCost &t, GemmLayout l, long wgs, int nk) {
