@@ -404,7 +404,7 @@ def measure_ceilings(dev, reps=3):
     props = torch.cuda.get_device_properties(dev)
     return {"mfma_bf16_tflops": round(mfma, 1), "copy_gbs": round(copy, 1),
             "compute_units": props.multi_processor_count,
-            "note": "best of 3; MFMA-only loop of v_mfma_f32_32x32x16_bf16 with changing operands; "
+            "note": "best of 3; MFMA-only loop of v_mfma_f32_16x16x32_bf16 with changing operands; "
                     "copy counts bytes read plus bytes written"}
 
 

@@ -543,9 +543,10 @@ int enc_schedule_kernels(const double *kernel_us, const int *kernel_comm, int n_
  * copy (the sustained HBM rate).  The caller times them with events on
  * `stream`; both follow the conventions above. */
 
-/* blocks x 256 threads; every wave issues iters x 16 independent
- * v_mfma_f32_32x32x16_bf16 on register operands whose mantissa bits change
- * every iteration, i.e. blocks * 4 * iters * 16 * 32768 flops.  One float
+/* blocks x 256 threads; every wave issues iters x 32
+ * v_mfma_f32_16x16x32_bf16 (the instruction of the projections' loops) on
+ * register operands whose mantissa bits change every iteration, i.e.
+ * blocks * 4 * iters * 32 * 16384 flops.  One float
  * per thread is written to out[blocks * 256] so that nothing is elided.
  * blocks, iters > 0. */
 int enc_calib_mfma(int blocks, int iters, float *out, enc_stream_t stream);

@@ -572,7 +572,7 @@ def enc_attn_bwd_noalloc(batch, seq, heads, head_dim, qkv, o, lse, do, dqkv, str
 # ---------------------------------------------------------------- measurement helpers
 
 def enc_calib_mfma(blocks, iters, out=None, stream=None, device="cuda"):
-    """MFMA-only reference loop: blocks * 4 * iters * 16 * 32768 flops."""
+    """MFMA-only reference loop: blocks * 4 * iters * 32 * 16384 flops."""
     if out is None:
         out = torch.empty(blocks * 256, dtype=torch.float32, device=device)
     _check(out, "out", (blocks * 256,), torch.float32)
@@ -581,7 +581,7 @@ def enc_calib_mfma(blocks, iters, out=None, stream=None, device="cuda"):
 
 
 def calib_mfma_flops(blocks, iters):
-    return blocks * 4 * iters * 16 * 32768
+    return blocks * 4 * iters * 32 * 16384
 
 
 def enc_calib_copy(src, dst, stream=None):

@@ -7,11 +7,14 @@ namespace optimus {
 
 namespace {
 
-// Every wave: iters x 16 independent 32x32x16 bf16 MFMAs.  Operands are bf16
-// pairs in [1, 2) (exponent fixed, so no overflow) whose mantissa bits are
-// re-drawn every iteration: a matrix core fed constant operands switches
-// less and runs at a higher clock than one fed real data.
-__global__ __launch_bounds__(256) void calib_mfma_kernel(int iters, float *__restrict__ out) {
+// Every wave: iters x 32 16x16x32 bf16 MFMAs (the instruction of the GEMMs'
+// loops), two into each of 16 accumulators.  Operands are bf16 pairs in [1, 2) (exponent fixed, so no
+// overflow) whose mantissa bits are re-drawn every iteration: a matrix core fed
+// constant operands switches less and runs at a higher clock than one fed real
+// data.
+constexpr int kCalibFrags = 16;
+
+__global__ __launch_bounds__(256, 4) void calib_mfma_kernel(int iters, float *__restrict__ out) {
   const uint32_t t = blockIdx.x * 256 + threadIdx.x;
   u32x4_t ua, ub;
 #pragma unroll
@@ -19,9 +22,9 @@ __global__ __launch_bounds__(256) void calib_mfma_kernel(int iters, float *__res
     ua[e] = 0x3F803F80u ^ ((t * 0x9E3779B9u + e * 0x85EBCA6Bu) & 0x007F007Fu);
     ub[e] = 0x3F803F80u ^ ((t * 0xC2B2AE35u + e * 0x27D4EB2Fu) & 0x007F007Fu);
   }
-  f32x16_t acc[16];
+  f32x4_t acc[kCalibFrags];
 #pragma unroll
-  for (int i = 0; i < 16; ++i) acc[i] = f32x16_t{};
+  for (int i = 0; i < kCalibFrags; ++i) acc[i] = f32x4_t{};
   for (int it = 0; it < iters; ++it) {
     const uint32_t m = (static_cast<uint32_t>(it) * 0x9E3779B9u) & 0x007F007Fu;
 #pragma unroll
@@ -31,13 +34,13 @@ __global__ __launch_bounds__(256) void calib_mfma_kernel(int iters, float *__res
     }
     const bf16x8_t a = as_bf16x8(ua), b = as_bf16x8(ub);
 #pragma unroll
-    for (int i = 0; i < 16; ++i) acc[i] = mfma32(a, b, acc[i]);
+    for (int i = 0; i < 2 * kCalibFrags; ++i) acc[i % kCalibFrags] = mfma16(a, b, acc[i % kCalibFrags]);
   }
   float s = 0.f;
 #pragma unroll
-  for (int i = 0; i < 16; ++i)
+  for (int i = 0; i < kCalibFrags; ++i)
 #pragma unroll
-    for (int e = 0; e < 16; ++e) s += acc[i][e];
+    for (int e = 0; e < 4; ++e) s += acc[i][e];
   out[t] = s;
 }
 

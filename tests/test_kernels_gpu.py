@@ -502,6 +502,10 @@ def test_calibration_kernels():
     assert torch.equal(dst.view(torch.uint8), src)
     assert guard_intact(buf, dst.numel())
     assert torch.isfinite(out).all() and (out > 0).all()
+    # a thread adds up 3 iterations of 32 fragments of 4 dot products over 32
+    # operand pairs, each product in [1, 4)
+    n = B.calib_mfma_flops(8, 3) // (2 * 8 * 256)
+    assert (out >= n).all() and (out < 4 * n).all()
 
 
 # --------------------------------------------------------------------------- maximum sizes
