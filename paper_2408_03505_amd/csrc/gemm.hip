@@ -599,19 +599,24 @@ bool launch_any(const GemmArgs &a, hipStream_t s) {
 // thus has 10 slots, 1.25 k-steps, before the wait that precedes its first
 // read, and up to 6 of the 8 half tiles in LDS are in flight.
 //
-// What bounds it: with the loop free of vector instructions other than MFMAs
-// and LDS reads (addresses in registers, scalar load addressing) the matrix
-// cores are busy 97% of the k-loop's cycles, and the clock falls to what the
-// power budget allows.  So the fragments are 16x16x32: in a register-only loop
-// over random data they ran 2.04 PFLOP/s against 1.80 for 32x32x16.  With
-// transpose reads (strided operands) the LDS pipe's instruction rate binds
-// next: about 4.3 cycles each, 24 per wave and k-step for one strided operand,
-// 36 or 48 for two.  Measured on the ViT-22B layer (us, against the kernels
-// this replaced, on 32x32x16 with a whole k-step per barrier): QKV forward
-// 401 -> 342, out-projection forward 136 -> 118, MLP-up forward 548 -> 473,
-// MLP-down forward 532 -> 451, MLP-down input gradient 540 -> 478, MLP-up
-// 551 -> 511, QKV 417 -> 391, weight gradients 526 -> 513, 537 -> 520,
-// 410 -> 397.
+// What bounds it: the loop holds no vector instructions other than MFMAs and LDS
+// reads (addresses in registers, scalar load addressing).  Over one round of
+// tiles and 1024 to 1920 k-steps, where starts and epilogues count for little,
+// the matrix cores are busy 0.91 of the cycles at a clock of 1.5 GHz (forward,
+// 256x256), 0.83 at 1.7 (forward, 256x192), 0.82 at 1.7 (input gradient) and
+// 0.72 at 1.85 (weight gradient), where the nominal clock is 2.4: the busier
+// they are, the lower the clock that the power budget leaves.  So the fragments
+// are 16x16x32: a register-only loop (enc_calib_mfma) runs 2.04 to 2.16 PFLOP/s
+// on them against 1.80 to 1.95 on 32x32x16.  With transpose reads (strided
+// operands) the LDS pipe's instruction rate binds next: about 4.3 cycles each,
+// 24 per wave and k-step for one strided operand, 36 or 48 for two.  In the
+// ViT-22B layer itself the products are at 0.49 to 0.77 busy: there their
+// rounds' starts and epilogues are not hidden.  Measured on that layer (us,
+// against the kernels this replaced, on 32x32x16 with a whole k-step per
+// barrier): QKV forward 401 -> 342, out-projection forward 136 -> 118, MLP-up
+// forward 548 -> 473, MLP-down forward 532 -> 451, MLP-down input gradient
+// 540 -> 478, MLP-up 551 -> 511, QKV 417 -> 391, weight gradients 526 -> 513,
+// 537 -> 520, 410 -> 397.
 // ---------------------------------------------------------------------------
 
 // One 1 KB wave load straight to LDS at base + OFF + 16 * lane.  M0 (the LDS
