@@ -132,14 +132,19 @@ def _split_item(pid, nb, tiles_m, tiles_n):
     return split, t % tiles_m, t // tiles_m
 
 
+L2_BYTES = 4 << 20  # of one XCD
+
+
 def fetch_floor(rows, cols, K, bm, bn, splits, staged=False):
     """Operand bytes the eight L2s must fetch at least for one GEMM launch
     (output rows x cols, contraction K, bf16 operands): the workgroups of a
     round run together (one per CU, two for the tiles that share one), the eighth of
     them on one XCD share its L2, and an operand panel (a tile row's or tile
-    column's slice of the contraction) outlives neither its round nor its
-    XCD.  Each round's distinct panels per XCD, summed.  staged: the
-    register-staged kernel runs the product (another tile order)."""
+    column's slice of the contraction) outlives neither its round nor its XCD.
+    Each round's distinct panels per XCD, summed; where a round's panels take
+    less than twice the L2 (short contractions), up to an L2's worth of those
+    that an earlier round read may still be there and is not counted.  staged:
+    the register-staged kernel runs the product (another tile order)."""
     gm = 4 if bm == 256 or staged else 8
     per_round = 512 if (bm, bn) in ((192, 128), (128, 128), (64, 128), (64, 64)) else 256
     tm, tn = -(-rows // bm), -(-cols // bn)
@@ -148,15 +153,20 @@ def fetch_floor(rows, cols, K, bm, bn, splits, staged=False):
     if splits > 1:
         kc = -(-kc // 64) * 64
     total = 0
+    seen = {}
     for r0 in range(0, nb, per_round):
         panels = {}
         for pid in range(r0, min(nb, r0 + per_round)):
             sp, a, b = _split_item(pid, nb, tm, tn) if splits > 1 else (0, *_tile_of(pid, nb, tm, tn, gm))
             klen = min(K - sp * kc, kc)
-            rs, cs = panels.setdefault(pid & 7, (set(), set()))
-            rs.add((a, sp, min(bm, rows - a * bm) * klen))
-            cs.add((b, sp, min(bn, cols - b * bn) * klen))
-        total += sum(2 * (sum(x[2] for x in rs) + sum(x[2] for x in cs)) for rs, cs in panels.values())
+            ps = panels.setdefault(pid & 7, set())
+            ps.add(("row", a, sp, 2 * min(bm, rows - a * bm) * klen))
+            ps.add(("col", b, sp, 2 * min(bn, cols - b * bn) * klen))
+        for xcd, ps in panels.items():
+            need = sum(x[3] for x in ps)
+            again = sum(x[3] for x in ps & seen.setdefault(xcd, set()))
+            total += need - (min(again, L2_BYTES) if need < 2 * L2_BYTES else 0)
+            seen[xcd] |= ps
     return total
 
 
@@ -1037,7 +1047,8 @@ def main():
         floors = gemm_fetch_floors(CONFIGS[args.config])
         print("`fetch floor`: for each GEMM, the operand bytes that the eight XCD caches must fetch at least "
               "under its launch plan, since each XCD's concurrent workgroups share one L2 and an operand "
-              "panel outlives neither its round of tiles nor its XCD.\n")
+              "panel outlives neither its round of tiles nor its XCD (where a round's panels take less than twice the "
+              "L2, up to an L2's worth of those read before may still be there).\n")
         print("| entry | FETCH bytes | WRITE bytes | traffic bytes | algorithmic bytes | traffic / algorithmic "
               "| fetch floor | FETCH / floor |")
         print("|---|---|---|---|---|---|---|---|")

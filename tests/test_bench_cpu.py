@@ -209,6 +209,25 @@ def test_split_order_model_covers_every_item_once(tm, tn, S):
     assert sorted(seen) == [(s, a, b) for s in range(S) for a in range(tm) for b in range(tn)]
 
 
+def test_fetch_floor_counts_panels_that_may_outlive_a_round_once():
+    # ViT-Base MLP-up forward, 50 x 24 tiles of 128x128 over K = 768: an XCD's
+    # 25 x 6 block in three rounds of 64 workgroups, whose panels take 4.3, 4.3
+    # and 2.0 MB, about the 4 MB L2: in all each panel is counted once
+    once = 4 * 2 * 768 * ((25 + 6) * 128 + (24 * 128 + 32 + 6 * 128))  # 6304 rows end in a tile of 32
+    assert bench.fetch_floor(6304, 3072, 768, 128, 128, 1) == once
+    # one round, a column of 8 tiles per XCD: nothing was there before
+    assert bench.fetch_floor(1024, 1024, 768, 128, 128, 1) == 8 * (8 + 1) * 128 * 768 * 2
+
+
+@pytest.mark.parametrize("name", ["vit22b", "vit22b_tp8", "vit_base", "vit_huge"])
+def test_profiles_fetch_no_less_than_the_floor(name):
+    with open(os.path.join(ROOT, "profiles", f"{name}_layer_hbm_traffic.md")) as f:
+        rows = [line.split("|")[1:-1] for line in f if line.startswith("| ")]
+    ratios = {r[0].strip(): float(r[7]) for r in rows if r[7].strip().replace(".", "").isdigit()}
+    assert len(ratios) == 12
+    assert all(v >= 0.99 for v in ratios.values()), ratios
+
+
 def test_fetch_floor_bounds():
     # ViT-22B MLP-up forward on 256x256 tiles: 8 x 96 tiles, three rounds; in
     # a round each XCD runs 4 row tiles x 8 column tiles and fetches those

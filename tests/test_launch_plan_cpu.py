@@ -92,9 +92,9 @@ def test_fetch_floors_are_those_of_the_tiles_that_run():
         assert floors[n] == bench.fetch_floor(M, F, H, *B.linear_plan(layout, M, F, H)), n
     # a contraction that is no multiple of 64: the register-staged kernel walks
     # its 128x128 tiles in groups of 4 rows, not 8
-    odd = dict(cfg, hidden=776, seq=256, batch=16)
-    assert bench.gemm_fetch_floors(odd)["mlp_up_fwd"] == bench.fetch_floor(4096, F, 776, 128, 128, 1, staged=True)
-    assert bench.fetch_floor(4096, F, 776, 128, 128, 1, staged=True) != bench.fetch_floor(4096, F, 776, 128, 128, 1)
+    odd = dict(cfg, hidden=3080, seq=256, batch=16)
+    assert bench.gemm_fetch_floors(odd)["mlp_up_fwd"] == bench.fetch_floor(4096, F, 3080, 128, 128, 1, staged=True)
+    assert bench.fetch_floor(4096, F, 3080, 128, 128, 1, staged=True) != bench.fetch_floor(4096, F, 3080, 128, 128, 1)
 
 
 @pytest.mark.parametrize("gm", (4, 8))
